@@ -22,7 +22,6 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 
 constexpr int JB = 16;  // block width
 constexpr int JW = 32;  // columns handled by one workgroup
-constexpr int JR = 64;  // rows staged per tile
 
 __device__ inline void tournament_pair(int round, int w, int N, int& a, int& b) {
     // circle method: player N-1 is fixed, the others rotate
@@ -75,40 +74,45 @@ __device__ inline bool jacobi_angle(double app, double aqq, double apq, double& 
 // reads its block from H and writes the rotated block to Hs, and rotates rows
 // t mod 16 and t mod 16 + 16 of R's column pair t / 16 in place -- one barrier
 // per step.  Runs at most `sweeps` sweeps (31 steps each),
-// fewer when a sweep applies no rotation.  256 threads; H is overwritten.
+// fewer when a sweep applies no rotation.  The first 256 threads of the
+// workgroup work, any others keep to the barriers; H is overwritten.
 __device__ void inner_jacobi(double (*H)[JW + 1], double (*Hs)[JW + 1], double (*R)[JW + 1], int sweeps,
                              int* rot_any) {
     const int tid = threadIdx.x;
     const int a = tid & 15, b = tid >> 4;
-    for (int t = tid; t < JW * JW; t += 256) R[t % JW][t / JW] = (t % JW == t / JW) ? 1.0 : 0.0;
+    const bool works = tid < 256;
+    if (works)
+        for (int t = tid; t < JW * JW; t += 256) R[t % JW][t / JW] = (t % JW == t / JW) ? 1.0 : 0.0;
     double (*Hc)[JW + 1] = H;
     double (*Hn)[JW + 1] = Hs;
     for (int sweep = 0; sweep < sweeps; ++sweep) {
         if (tid == 0) *rot_any = 0;
         __syncthreads();
         for (int rr = 0; rr < JW - 1; ++rr) {
-            int pa, qa, pb, qb;
-            tournament_pair(rr, a, JW, pa, qa);
-            tournament_pair(rr, b, JW, pb, qb);
-            double ca, sa;
-            const bool rot = jacobi_angle(Hc[pa][pa], Hc[qa][qa], Hc[pa][qa], ca, sa);
-            // lane b (b < 16) of every wave computed the rotation of pair b
-            const double cb = __shfl(ca, b, 64), sb = __shfl(sa, b, 64);
-            if (rot) *rot_any = 1;
-            // block (a, b): T = H J_b on the columns, then J_a^T T on the rows
-            const double h11 = Hc[pa][pb], h12 = Hc[pa][qb], h21 = Hc[qa][pb], h22 = Hc[qa][qb];
-            const double t11 = cb * h11 - sb * h12, t12 = sb * h11 + cb * h12;
-            const double t21 = cb * h21 - sb * h22, t22 = sb * h21 + cb * h22;
-            Hn[pa][pb] = ca * t11 - sa * t21;
-            Hn[pa][qb] = ca * t12 - sa * t22;
-            Hn[qa][pb] = sa * t11 + ca * t21;
-            Hn[qa][qb] = sa * t12 + ca * t22;
+            if (works) {
+                int pa, qa, pb, qb;
+                tournament_pair(rr, a, JW, pa, qa);
+                tournament_pair(rr, b, JW, pb, qb);
+                double ca, sa;
+                const bool rot = jacobi_angle(Hc[pa][pa], Hc[qa][qa], Hc[pa][qa], ca, sa);
+                // lane b (b < 16) of every wave computed the rotation of pair b
+                const double cb = __shfl(ca, b, 64), sb = __shfl(sa, b, 64);
+                if (rot) *rot_any = 1;
+                // block (a, b): T = H J_b on the columns, then J_a^T T on the rows
+                const double h11 = Hc[pa][pb], h12 = Hc[pa][qb], h21 = Hc[qa][pb], h22 = Hc[qa][qb];
+                const double t11 = cb * h11 - sb * h12, t12 = sb * h11 + cb * h12;
+                const double t21 = cb * h21 - sb * h22, t22 = sb * h21 + cb * h22;
+                Hn[pa][pb] = ca * t11 - sa * t21;
+                Hn[pa][qb] = ca * t12 - sa * t22;
+                Hn[qa][pb] = sa * t11 + ca * t21;
+                Hn[qa][qb] = sa * t12 + ca * t22;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int i = a + 16 * h;
-                const double rp = R[i][pb], rq = R[i][qb];
-                R[i][pb] = cb * rp - sb * rq;
-                R[i][qb] = sb * rp + cb * rq;
+                for (int h = 0; h < 2; ++h) {
+                    const int i = a + 16 * h;
+                    const double rp = R[i][pb], rq = R[i][qb];
+                    R[i][pb] = cb * rp - sb * rq;
+                    R[i][qb] = sb * rp + cb * rq;
+                }
             }
             __syncthreads();
             double (*tmp)[JW + 1] = Hc;
@@ -117,6 +121,168 @@ __device__ void inner_jacobi(double (*H)[JW + 1], double (*Hs)[JW + 1], double (
         }
         if (!*rot_any) break;
         __syncthreads();
+    }
+}
+
+// ---- cross rotations of one block pair by one wave, all in registers ----------
+template <int CTRL>
+__device__ inline double dpp_mov(double v) {
+    const long long x = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(x), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(x >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
+}
+// the value held by lane ^ X
+template <int X>
+__device__ __forceinline__ double lane_xor(double v) {
+    if constexpr (X == 1) return dpp_mov<0xB1>(v);        // quad_perm [1,0,3,2]
+    else if constexpr (X == 2) return dpp_mov<0x4E>(v);   // quad_perm [2,3,0,1]
+    else if constexpr (X == 8) return dpp_mov<0x128>(v);  // row_ror:8
+    else return __shfl_xor(v, X, 64);
+}
+
+// The state of the cross rotations: lane (g, l) = (lane / 16, lane % 16) holds,
+// for a = l ^ 4g and the four b = 4g + q, the entries of H at the rows a and
+// 16 + (a ^ s) and the columns b and 16 + (b ^ s) of the current step's pairing
+// i <-> 16 + (i ^ s), and the entries of R at the rows l and 16 + l of those
+// columns; d1, d2, e are the pair a's own 2 x 2 block (replicated in the four
+// lanes that share a).
+struct CrossState {
+    double h11[4], h12[4], h21[4], h22[4], r11[4], r12[4], r21[4], r22[4], d1, d2, e;
+};
+
+// One step: the 16 disjoint rotations (i, 16 + (i ^ s)), then, unless it was
+// the last, the move to the pairing s ^ D.  Only the entries whose row or
+// column partner changes move: by register renaming where D touches the two
+// low bits of b, by DPP where it touches a within a row of 16 lanes, through
+// the LDS crossbar for the three of the 16 steps with D = 4 or 8.
+template <int D>
+__device__ __forceinline__ void cross_step(CrossState& z, int src) {
+    const int lane = threadIdx.x & 63;
+    // the rotation of pair a (as jacobi_angle, without its early exit)
+    const bool rot = z.e * z.e > 4.930380657631324e-32 * fabs(z.d1 * z.d2) && z.e != 0.0;
+    const double x = z.d2 - z.d1, y = 2.0 * z.e;
+    const double rr = fma(x, x, y * y);
+    double rs = __builtin_amdgcn_rsq(rr);
+    rs = rs * fma(-0.5 * rr * rs, rs, 1.5);
+    const double den = fabs(x) + rr * rs;
+    double rd = __builtin_amdgcn_rcp(den);
+    rd = rd * fma(-den, rd, 2.0);
+    const double t = rot ? (x >= 0.0 ? y : -y) * rd : 0.0;
+    const double u = fma(t, t, 1.0);
+    double rc = __builtin_amdgcn_rsq(u);
+    rc = rc * fma(-0.5 * u * rc, rc, 1.5);
+    rc = rc * fma(-0.5 * u * rc, rc, 1.5);
+    const double ca = rot ? rc : 1.0, sa = t * ca;
+    z.d1 -= t * z.e;
+    z.d2 += t * z.e;
+    // the rotation of pair b = 4g + q sits in lane q of the row (a = q ^ 4g = b)
+    const double cb[4] = {dpp_mov<0x150>(ca), dpp_mov<0x151>(ca), dpp_mov<0x152>(ca), dpp_mov<0x153>(ca)};
+    const double sb[4] = {dpp_mov<0x150>(sa), dpp_mov<0x151>(sa), dpp_mov<0x152>(sa), dpp_mov<0x153>(sa)};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const double t11 = cb[q] * z.h11[q] - sb[q] * z.h12[q], t12 = sb[q] * z.h11[q] + cb[q] * z.h12[q];
+        const double t21 = cb[q] * z.h21[q] - sb[q] * z.h22[q], t22 = sb[q] * z.h21[q] + cb[q] * z.h22[q];
+        z.h11[q] = ca * t11 - sa * t21;
+        z.h12[q] = ca * t12 - sa * t22;
+        z.h21[q] = sa * t11 + ca * t21;
+        z.h22[q] = sa * t12 + ca * t22;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const double p1 = z.r11[q], p2 = z.r12[q], p3 = z.r21[q], p4 = z.r22[q];
+        z.r11[q] = cb[q] * p1 - sb[q] * p2;
+        z.r12[q] = sb[q] * p1 + cb[q] * p2;
+        z.r21[q] = cb[q] * p3 - sb[q] * p4;
+        z.r22[q] = sb[q] * p3 + cb[q] * p4;
+    }
+    if constexpr (D != 0) {
+        double a12[4], a22[4], b12[4], b22[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if constexpr (D < 4) {
+                a12[q] = z.h12[q ^ D];
+                a22[q] = lane_xor<D>(z.h22[q ^ D]);
+                b12[q] = z.r12[q ^ D];
+                b22[q] = z.r22[q ^ D];
+            } else {
+                a12[q] = lane_xor<5 * D>(z.h12[q]);
+                a22[q] = lane_xor<4 * D>(z.h22[q]);
+                b12[q] = lane_xor<4 * D>(z.r12[q]);
+                b22[q] = lane_xor<4 * D>(z.r22[q]);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            z.h12[q] = a12[q];
+            z.h21[q] = lane_xor<D>(z.h21[q]);
+            z.h22[q] = a22[q];
+            z.r12[q] = b12[q];
+            z.r22[q] = b22[q];
+        }
+        z.d2 = lane_xor<D>(z.d2);
+        // the pair a's new off-diagonal entry sits at b = a: row a / 4, lane and q = a % 4
+        const double e01 = (lane & 1) ? z.h12[1] : z.h12[0], e23 = (lane & 1) ? z.h12[3] : z.h12[2];
+        z.e = __shfl((lane & 2) ? e23 : e01, src, 64);
+    }
+}
+
+// One pass of Jacobi rotations over the 256 pairs (i, 16 + j) of the 32 x 32
+// symmetric H between its two blocks of 16 -- 16 steps of 16 disjoint
+// rotations, pairing i with i ^ s, s in Gray-code order -- accumulated into R
+// (written whole).  The pairs within a block need a visit once per sweep only
+// (inner_jacobi does it in the sweep's first round), so a round's chain of
+// dependent steps is 16 instead of 31: simulated on NT factors and scaling
+// matrices (n = 48 .. 300), a decomposition takes 0 to 2 more sweeps of 8 to
+// 17.  Bound by the latency of that chain (the angle's ~25 dependent FP64
+// operations per step); one wave with everything in registers needs no barrier
+// and no LDS round trip in it.  At n = 1000 the pair kernel went from 19.9 to
+// 9.9 us per round and a scaling point from 74.9 to 53.8 ms.  Wave 0 of the
+// workgroup calls this; H is only read.
+__device__ __forceinline__ void cross_jacobi(const double (*H)[JW + 1], double (*R)[JW + 1]) {
+    const int lane = threadIdx.x & 63, l = lane & 15, g = lane >> 4, a = l ^ (4 * g);
+    const int src = 16 * (a >> 2) + (a & 3);
+    CrossState z;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int b = 4 * g + q;
+        z.h11[q] = H[a][b];
+        z.h12[q] = H[a][16 + b];
+        z.h21[q] = H[16 + a][b];
+        z.h22[q] = H[16 + a][16 + b];
+        z.r11[q] = l == b ? 1.0 : 0.0;
+        z.r12[q] = 0.0;
+        z.r21[q] = 0.0;
+        z.r22[q] = l == b ? 1.0 : 0.0;
+    }
+    z.d1 = H[a][a];
+    z.d2 = H[16 + a][16 + a];
+    z.e = H[a][16 + a];
+    // Gray code: step t pairs with s = t ^ (t >> 1), so D is the lowest set bit of t + 1
+    cross_step<1>(z, src);
+    cross_step<2>(z, src);
+    cross_step<1>(z, src);
+    cross_step<4>(z, src);
+    cross_step<1>(z, src);
+    cross_step<2>(z, src);
+    cross_step<1>(z, src);
+    cross_step<8>(z, src);
+    cross_step<1>(z, src);
+    cross_step<2>(z, src);
+    cross_step<1>(z, src);
+    cross_step<4>(z, src);
+    cross_step<1>(z, src);
+    cross_step<2>(z, src);
+    cross_step<1>(z, src);
+    cross_step<0>(z, src);
+    constexpr int s = 15 ^ (15 >> 1);  // the last step's pairing
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int b = 4 * g + q;
+        R[l][b] = z.r11[q];
+        R[l][16 + (b ^ s)] = z.r12[q];
+        R[16 + l][b] = z.r21[q];
+        R[16 + l][16 + (b ^ s)] = z.r22[q];
     }
 }
 
@@ -188,7 +354,7 @@ __global__ __launch_bounds__(256) void jacobi_gram_kernel(int n, int nblk, int r
 __global__ __launch_bounds__(256) void jacobi_pair_kernel(int nchunks, const double* __restrict__ part,
                                                           double* __restrict__ Rout, int* __restrict__ skip,
                                                           double tol, unsigned long long* offmax,
-                                                          const int* __restrict__ done, int inner_sweeps) {
+                                                          const int* __restrict__ done, int inner_sweeps, int round) {
     if (*done) return;
     __shared__ double H[JW][JW + 1], Hs[JW][JW + 1], R[JW][JW + 1];
     __shared__ double red[4];
@@ -243,7 +409,12 @@ __global__ __launch_bounds__(256) void jacobi_pair_kernel(int nchunks, const dou
     if (off_pair <= tol) return;  // uniform across the workgroup
     // The pair need not be diagonalised exactly: the outer sweeps revisit it,
     // and convergence is judged only by the tolerance test above.
-    inner_jacobi(H, Hs, R, inner_sweeps, &rot_any);
+    if (round == 0 || inner_sweeps > 1) {
+        inner_jacobi(H, Hs, R, inner_sweeps, &rot_any);
+    } else {
+        if (wave == 0) cross_jacobi(H, R);
+        __syncthreads();
+    }
     for (int t = tid; t < JW * JW; t += 256) Rout[(long)w * (JW * JW) + t] = R[t / JW][t % JW];
 }
 
@@ -308,13 +479,22 @@ __global__ __launch_bounds__(256) void jacobi_rotate_kernel(int n, int nblk, int
 // stay in LDS for the whole round -- loaded once, used for the Gram matrix
 // and for the rotation.  Used when 2 * 32 * (n + 1) doubles plus the 32 x 32
 // work arrays fit in the workgroup's LDS.
+//
+// A round has only nblk / 2 workgroups (7 at n = 200), so it is bound by the
+// latency of one workgroup's chain: load, Gram matrix, inner rotations,
+// rotation.  Eight waves: the first four take A, the others V, whose loads
+// land while the Gram matrix forms.  At n = 200 a round takes 16.5 us; it was
+// 27.8 us with all 496 pairs rotated in every round and four waves walking A,
+// then V.
 // ---------------------------------------------------------------------------
 __host__ __device__ inline int jl_ld(int n) { return ((n + 15) / 16) * 16 + 1; }  // odd pitch: fewer bank conflicts
 
-__global__ __launch_bounds__(256) void jacobi_round_lds_kernel(int n, int nblk, int round, double* __restrict__ A,
-                                                               long lda, double* __restrict__ V, long ldv, double tol,
-                                                               unsigned long long* offmax,
-                                                               const int* __restrict__ done, int inner_sweeps) {
+constexpr int JT = 512;  // threads of the small-n round
+
+__global__ __launch_bounds__(JT) void jacobi_round_lds_kernel(int n, int nblk, int round, double* __restrict__ A,
+                                                              long lda, double* __restrict__ V, long ldv, double tol,
+                                                              unsigned long long* offmax,
+                                                              const int* __restrict__ done, int inner_sweeps) {
     if (*done) return;
     extern __shared__ double jl[];
     const int ldb = jl_ld(n);
@@ -322,7 +502,6 @@ __global__ __launch_bounds__(256) void jacobi_round_lds_kernel(int n, int nblk, 
     double* Ab = jl;                           // [32][ldb]: column c at Ab + c * ldb
     double* Vb = jl + JW * ldb;                // same for V (when V != nullptr)
     __shared__ double H0[JW][JW + 1], H1[JW][JW + 1], R[JW][JW + 1];
-    __shared__ int cols[JW];
     __shared__ double red[4];
     __shared__ int rot_any;
 
@@ -330,99 +509,115 @@ __global__ __launch_bounds__(256) void jacobi_round_lds_kernel(int n, int nblk, 
     const int lane = tid & 63, wave = tid >> 6;
     int bi, bj;
     tournament_pair(round, blockIdx.x, nblk, bi, bj);
-    if (tid < JW) {
-        int c = (tid < JB) ? bi * JB + tid : bj * JB + (tid - JB);
-        cols[tid] = (c < n) ? c : -1;
-    }
-    __syncthreads();
-    // ---- load both column blocks of A and of V: thread `row` holds all its
-    // loads in flight at once (nr <= 256 whenever this kernel is selected,
-    // so one row per thread)
-    if (tid < nr) {
-        const int row = tid;
-        double ta[JW], tv[JW];
+    auto col = [&](int c) { return c < JB ? bi * JB + c : bj * JB + (c - JB); };  // >= n in the padding
+    // ---- both column blocks of A (threads 0..255) and of V (256..511): thread
+    // `row` holds all its loads in flight at once (nr <= 256 whenever this
+    // kernel is selected, so one row per thread); V is stored after the
+    // barrier that releases the Gram matrix
+    const bool mine = tid < 256;
+    const double* Ms = mine ? A : V;
+    double* Mb = mine ? Ab : Vb;
+    const int row = tid & 255;
+    double tv[JW];
+    if (Ms != nullptr && row < nr) {
+        const long ldm = mine ? lda : ldv;
 #pragma unroll
         for (int u = 0; u < JW; ++u) {
-            const int gc = cols[u];
-            ta[u] = (gc >= 0 && row < n) ? A[row + (long)gc * lda] : 0.0;
+            const int gc = col(u);
+            tv[u] = (gc < n && row < n) ? Ms[row + (long)gc * ldm] : 0.0;
         }
-        if (V) {
+        if (mine) {
 #pragma unroll
-            for (int u = 0; u < JW; ++u) {
-                const int gc = cols[u];
-                tv[u] = (gc >= 0 && row < n) ? V[row + (long)gc * ldv] : 0.0;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < JW; ++u) Ab[u * ldb + row] = ta[u];
-        if (V) {
-#pragma unroll
-            for (int u = 0; u < JW; ++u) Vb[u * ldb + row] = tv[u];
+            for (int u = 0; u < JW; ++u) Mb[u * ldb + row] = tv[u];
         }
     }
     __syncthreads();
 
-    // ---- 1. Gram matrix from LDS ----------------------------------------------
-    {
+    // ---- 1. Gram matrix from LDS (waves 0..3, one 16 x 16 tile each) -------------
+    if (mine) {
         const int hi = wave >> 1, hj = wave & 1;
         // two accumulators halve the dependent MFMA chain (nr is a multiple of 16)
         d4 acc = {0.0, 0.0, 0.0, 0.0}, acc2 = {0.0, 0.0, 0.0, 0.0};
         const double* ca = Ab + (hi * 16 + (lane & 15)) * ldb + (lane >> 4);
         const double* cb = Ab + (hj * 16 + (lane & 15)) * ldb + (lane >> 4);
-#pragma unroll 2
-        for (int k4 = 0; k4 < nr; k4 += 8) {
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ca[k4], cb[k4], acc, 0, 0, 0);
-            acc2 = __builtin_amdgcn_mfma_f64_16x16x4f64(ca[k4 + 4], cb[k4 + 4], acc2, 0, 0, 0);
+        for (int k4 = 0; k4 < nr; k4 += 16) {
+            double x[4], y[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                x[u] = ca[k4 + 4 * u];
+                y[u] = cb[k4 + 4 * u];
+            }
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[0], y[0], acc, 0, 0, 0);
+            acc2 = __builtin_amdgcn_mfma_f64_16x16x4f64(x[1], y[1], acc2, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(x[2], y[2], acc, 0, 0, 0);
+            acc2 = __builtin_amdgcn_mfma_f64_16x16x4f64(x[3], y[3], acc2, 0, 0, 0);
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) H0[hi * 16 + (lane >> 4) + 4 * v][hj * 16 + (lane & 15)] = acc[v] + acc2[v];
+    } else if (V != nullptr && row < nr) {
+#pragma unroll
+        for (int u = 0; u < JW; ++u) Mb[u * ldb + row] = tv[u];
     }
     __syncthreads();
 
     // ---- convergence measure of this pair ----------------------------------
-    double mx = 0.0;
-    for (int t = tid; t < JW * JW; t += 256) {
-        const int i = t % JW, j = t / JW;
-        if (i < j) {
-            const double hii = H0[i][i], hjj = H0[j][j];
-            if (hii > 0.0 && hjj > 0.0) mx = fmax(mx, H0[i][j] * H0[i][j] / (hii * hjj));  // squared
-        }
-    }
+    if (mine) {
+        double mx = 0.0;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
-    if (lane == 0) red[wave] = mx;
+        for (int t = tid; t < JW * JW; t += 256) {
+            const int i = t % JW, j = t / JW;
+            if (i < j) {
+                const double hii = H0[i][i], hjj = H0[j][j];
+                if (hii > 0.0 && hjj > 0.0) mx = fmax(mx, H0[i][j] * H0[i][j] / (hii * hjj));  // squared
+            }
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
+        if (lane == 0) red[wave] = mx;
+    }
     __syncthreads();
     const double off_pair = sqrt(fmax(fmax(red[0], red[1]), fmax(red[2], red[3])));
     if (tid == 0) atomicMax(offmax, static_cast<unsigned long long>(__double_as_longlong(off_pair)));
     if (off_pair <= tol) return;  // uniform across the workgroup; A and V unchanged
 
     // ---- 2. two-sided Jacobi on H (at most inner_sweeps sweeps) --------------
-    inner_jacobi(H0, H1, R, inner_sweeps, &rot_any);
+    if (round == 0 || inner_sweeps > 1) {
+        inner_jacobi(H0, H1, R, inner_sweeps, &rot_any);
+    } else {
+        if (wave == 0) cross_jacobi(H0, R);
+        __syncthreads();
+    }
 
-    // ---- 3. [A_i A_j] <- [A_i A_j] R and likewise V, from LDS to global -------
-    for (int pass = 0; pass < 2; ++pass) {
-        double* M = pass == 0 ? A : V;
-        const double* Mb = pass == 0 ? Ab : Vb;
-        const long ldm = pass == 0 ? lda : ldv;
-        if (M == nullptr) break;
-        for (int rt = wave; rt < nr / 16; rt += 4) {
-            const int r0 = rt * 16;
+    // ---- 3. [A_i A_j] <- [A_i A_j] R and likewise V, from LDS to global: the
+    // transposed product, so that a store covers 16 consecutive rows of a column
+    {
+        double* M = mine ? A : V;
+        const long ldm = mine ? lda : ldv;
+        if (M == nullptr) return;
+        double rv[2][JW / 4];
 #pragma unroll
-            for (int jt = 0; jt < 2; ++jt) {
-                d4 o = {0.0, 0.0, 0.0, 0.0};
+        for (int jt = 0; jt < 2; ++jt)
 #pragma unroll
-                for (int k4 = 0; k4 < JW; k4 += 4) {
-                    const int k = k4 + (lane >> 4);
-                    const double a = Mb[k * ldb + r0 + (lane & 15)];
-                    const double b = R[k][jt * 16 + (lane & 15)];
-                    o = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, o, 0, 0, 0);
-                }
-                const int gc = cols[jt * 16 + (lane & 15)];
+            for (int k4 = 0; k4 < JW; k4 += 4) rv[jt][k4 / 4] = R[k4 + (lane >> 4)][jt * 16 + (lane & 15)];
+        for (int rt = wave & 3; rt < nr / 16; rt += 4) {
+            const int grow = rt * 16 + (lane & 15);
+            d4 o[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};
+            double mv[JW / 4];
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int row = r0 + (lane >> 4) + 4 * v;
-                    if (gc >= 0 && row < n) M[row + (long)gc * ldm] = o[v];
-                }
+            for (int k4 = 0; k4 < JW; k4 += 4) mv[k4 / 4] = Mb[(k4 + (lane >> 4)) * ldb + grow];
+#pragma unroll
+            for (int k = 0; k < JW / 4; ++k)
+#pragma unroll
+                for (int jt = 0; jt < 2; ++jt)
+                    o[jt] = __builtin_amdgcn_mfma_f64_16x16x4f64(rv[jt][k], mv[k], o[jt], 0, 0, 0);
+            if (grow < n) {
+#pragma unroll
+                for (int jt = 0; jt < 2; ++jt)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int gc = col(jt * 16 + (lane >> 4) + 4 * v);
+                        if (gc < n) M[grow + (long)gc * ldm] = o[jt][v];
+                    }
             }
         }
     }
@@ -574,7 +769,7 @@ static void split_round(hipStream_t st, int n, int nblk, int round, double* A, l
                        w.part.get(), flags);
     WC_LAUNCH_CHECK();
     hipLaunchKernelGGL(jacobi_pair_kernel, dim3(npairs), dim3(256), 0, st, nchunks, w.part.get(), w.rot.get(),
-                       w.skip.get(), tol, off, flags, jacobi_inner_sweeps());
+                       w.skip.get(), tol, off, flags, jacobi_inner_sweeps(), round);
     WC_LAUNCH_CHECK();
     hipLaunchKernelGGL(jacobi_rotate_kernel, dim3(npairs, nchunks, V ? 2 : 1), dim3(256), 0, st, n, nblk, round, A,
                        lda, V, ldv, w.rot.get(), w.skip.get(), flags);
@@ -610,7 +805,7 @@ int jacobi_svd(hipStream_t st, int n, double* A, long lda, double* V, long ldv, 
     for (int s = 0; s < max_sweeps && !done; ++s) {
         for (int round = 0; round < nblk - 1; ++round) {
             if (use_lds)
-                hipLaunchKernelGGL(jacobi_round_lds_kernel, dim3(nblk / 2), dim3(256), lds_dyn, st, n, nblk, round, A,
+                hipLaunchKernelGGL(jacobi_round_lds_kernel, dim3(nblk / 2), dim3(JT), lds_dyn, st, n, nblk, round, A,
                                    lda, V, ldv, tol, off, flags, jacobi_inner_sweeps());
             else
                 split_round(st, n, nblk, round, A, lda, V, ldv, tol, off, flags, w);

@@ -1,0 +1,36 @@
+"""Edge sizes of the HIP kernels whose split or route depends on the size.
+
+Each test compares against NumPy / the oracle's formulas with a bound for FP64
+sums of the length involved (c * K * eps times the operands' size).
+"""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from paper_2407_14013_amd import linalg as la  # noqa: E402
+
+EPS = 2.0 ** -53
+
+
+@pytest.mark.parametrize("n", [31, 32, 33, 48, 49, 208, 255, 256, 258, 289])
+def test_jacobi_clustered_and_zero_columns(n):
+    # block pairs with equal eigenvalues (rotation angles of 45 degrees and
+    # none at all), a zero column (nothing to rotate) and padded columns: the
+    # rounds past a sweep's first rotate only between the two blocks of a pair
+    rng = np.random.default_rng(n)
+    Q1, _ = np.linalg.qr(rng.standard_normal((n, n)))
+    Q2, _ = np.linalg.qr(rng.standard_normal((n, n)))
+    d = np.repeat([4.0, 1.0, 0.25], [n // 3, n // 3, n - 2 * (n // 3)])
+    A = (Q1 * d) @ Q2.T
+    A[:, n // 2] = 0.0
+    Ad = la.to_dev(A)
+    s, V, sweeps = la.djacobi_svd(Ad)
+    s, Vg, Aout = s.cpu().numpy(), la.from_dev(V), la.from_dev(Ad)
+    ref = np.linalg.svd(A, compute_uv=False)
+    assert 1 <= sweeps <= 60  # the call's own limit: clusters converge slowly (28 to 43 sweeps past n = 200)
+    assert np.abs(s - ref).max() <= 20 * n * EPS * ref[0]
+    assert np.abs(Vg.T @ Vg - np.eye(n)).max() <= 20 * n * EPS
+    assert np.abs(A @ Vg - Aout).max() <= 20 * n * EPS * ref[0]

@@ -412,8 +412,8 @@ typedef struct sdp_batch_tune {
  * n_i <= 128 recommended (every workgroup keeps O(n^2 + m d + d^2) doubles of
  * scratch).  results: count entries (time_ms is the whole launch).  X_out,
  * y_out: NULL or host arrays of `count` device pointers (NULL entries
- * allowed) receiving X_i (n_i x n_i) and y_i (m_i).  tune: NULL (defaults) or
- * `count` configurations.  Uses opt's rank_max, inner_tol, inner_maxit,
+ * allowed) receiving X_i (n_i x n_i) and y_i (m_i).  tune: NULL (chosen by
+ * each instance's size) or `count` configurations.  Uses opt's rank_max, inner_tol, inner_maxit,
  * gap_tol, feas_tol, max_ipm_iter and step_frac; status per instance in
  * results[i].status.
  */

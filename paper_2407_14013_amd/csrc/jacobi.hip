@@ -15,6 +15,7 @@
 #include <cstdlib>
 
 #include "common.hpp"
+#include "wave.hpp"
 
 namespace wc {
 
@@ -125,13 +126,6 @@ __device__ void inner_jacobi(double (*H)[JW + 1], double (*Hs)[JW + 1], double (
 }
 
 // ---- cross rotations of one block pair by one wave, all in registers ----------
-template <int CTRL>
-__device__ inline double dpp_mov(double v) {
-    const long long x = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(x), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(x >> 32), CTRL, 0xf, 0xf, true);
-    return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
-}
 // the value held by lane ^ X
 template <int X>
 __device__ __forceinline__ double lane_xor(double v) {

@@ -12,15 +12,16 @@
 
 #include "common.hpp"
 #include "lanczos.hpp"
+#include "wave.hpp"
 
 namespace wc {
 
 constexpr int LZ_THREADS = 1024;
 constexpr int LZ_WAVES = LZ_THREADS / 64;
+constexpr int LZ_TREG = 24;  // columns of its chunk of T that a thread keeps in registers
 
 __device__ inline double lz_block_sum(double v, double* red) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    v = wave_sum_all(v);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     __syncthreads();
     if (lane == 0) red[wv] = v;
@@ -34,39 +35,135 @@ __device__ inline double lz_block_sum(double v, double* red) {
 // The start vector: deterministic, with no special structure.
 __device__ inline double lz_start(int i) { return 1.0 + 0.5 * sin(1.0 + 0.7071067811865476 * i) + 0.25 * cos(0.3 * i * i); }
 
-// Dynamic LDS layout: q (n), w (n), partial products of the matrix-vector
+// Smallest eigenvalue of the k x k tridiagonal (ta, tb) in LDS, by multisection
+// of its Gershgorin interval: every thread counts the eigenvalues below one
+// point per round (Sturm sequence).  It only decides whether the Ritz value
+// has settled to 1e-10 of the norm, so four rounds (1025^4 = 1e12 intervals)
+// and a refined hardware reciprocal in the recurrence are enough; the division
+// and the two further rounds that it took before were a third of the kernel's
+// time (n = 200).  All threads of the workgroup call this.
+__device__ __forceinline__ double lz_smallest(const double* ta, const double* tb, int k, int* first_hit) {
+    const int tid = threadIdx.x;
+    double lo = ta[0], hi = ta[0];
+    for (int i = 0; i < k; ++i) {
+        const double rr = (i > 0 ? fabs(tb[i - 1]) : 0.0) + (i + 1 < k ? fabs(tb[i]) : 0.0);
+        lo = fmin(lo, ta[i] - rr);
+        hi = fmax(hi, ta[i] + rr);
+    }
+    for (int round = 0; round < 4; ++round) {
+        const double step = (hi - lo) / (LZ_THREADS + 1);
+        const double x = lo + (tid + 1) * step;
+        int cnt = 0;
+        double dd = 1.0, bb = 0.0;
+        for (int i = 0; i < k; ++i) {
+            double rd = __builtin_amdgcn_rcp(dd);
+            rd = rd * fma(-dd, rd, 2.0);
+            dd = ta[i] - x - bb * rd;
+            bb = tb[i] * tb[i];
+            if (fabs(dd) < 1e-300) dd = -1e-300;
+            if (dd < 0.0) ++cnt;
+        }
+        if (tid == 0) *first_hit = LZ_THREADS;
+        __syncthreads();
+        if (cnt >= 1) atomicMin(first_hit, tid);
+        __syncthreads();
+        const int t = *first_hit;
+        __syncthreads();
+        const double nlo = lo + t * step, nhi = (t < LZ_THREADS) ? lo + (t + 1) * step : hi;
+        lo = nlo;
+        hi = nhi;
+    }
+    return 0.5 * (lo + hi);
+}
+
+// h[l] = Q(:, l) . w for l <= j: wave v takes l = v, v + 16, ... (at most four
+// of them, together, so that their reductions overlap).
+__device__ __forceinline__ void lz_project(int n, int j, const double* Q, long ldq, const double* w, double* h) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    constexpr int NL = LZ_MAX_K / LZ_WAVES;
+    double s[NL];
+#pragma unroll
+    for (int u = 0; u < NL; ++u) s[u] = 0.0;
+    if (wv <= j) {
+        for (int i = lane; i < n; i += 64) {
+            const double wi = w[i];
+#pragma unroll
+            for (int u = 0; u < NL; ++u)
+                if (wv + LZ_WAVES * u <= j) s[u] += Q[i + (long)(wv + LZ_WAVES * u) * ldq] * wi;
+        }
+#pragma unroll
+        for (int u = 0; u < NL; ++u) s[u] = wave_sum_all(s[u]);
+        if (lane == 0) {
+#pragma unroll
+            for (int u = 0; u < NL; ++u)
+                if (wv + LZ_WAVES * u <= j) h[wv + LZ_WAVES * u] = s[u];
+        }
+    }
+    __syncthreads();
+}
+
+// sum over l = l0, l0 + dl, ... <= j of h[l] Q(i, l), eight loads in flight
+__device__ __forceinline__ double lz_combine(int i, int j, int l0, int dl, const double* Q, long ldq, const double* h) {
+    double v = 0.0;
+    int l = l0;
+    for (; l + 7 * dl <= j; l += 8 * dl) {
+        double x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = Q[i + (long)(l + u * dl) * ldq];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v += h[l + u * dl] * x[u];
+    }
+    for (; l <= j; l += dl) v += h[l] * Q[i + (long)l * ldq];
+    return v;
+}
+
+// Dynamic LDS layout: q (n, then LZ_TREG zeros), w (n), partial products of the matrix-vector
 // product (LZ_THREADS, only when rows are split into chunks), and, when it
-// fits (qlds != 0), the Lanczos basis (n x (kmax + 1)).  Otherwise the basis
+// fits (QLDS), the Lanczos basis (n x (kmax + 1)).  Otherwise the basis
 // lives in the global buffer Qg.
 //
 // The product w = T q splits each row into `nch` column chunks so that all
 // threads take part: thread t < n * nch forms the partial sum of row t % n
-// over chunk t / n, and the partials are added in chunk order.
+// over chunk t / n, and the partials are added in chunk order.  A thread
+// keeps the first LZ_TREG columns of its part of T in registers for the whole
+// run (more of them spill at 1024 threads), so a step reads only the rest from
+// L2: 2 of 5 columns at n = 200, none up to n = 156.
+// The second half of a reorthogonalisation pass is split over the same chunks.
+// A step is a chain of about ten phases of one workgroup, bound by their
+// latency.  At n = 200 a launch of two runs takes 660 us; it took 1030 us with
+// T read from L2 in every step, one thread per row subtracting the projections
+// one after another, sums through the LDS crossbar and the Ritz value found
+// with divisions (n = 301: 875 and 1057 us).
 // Workgroup b of the launch works on T_b (T0 or T1) with its own basis
 // buffer, coefficients and step count.
+template <bool QLDS>
 __global__ __launch_bounds__(LZ_THREADS) void lanczos_kernel(int n, const double* __restrict__ T0,
                                                              const double* __restrict__ T1, long ldt, int kmax,
-                                                             double* __restrict__ Qg, int qlds,
-                                                             double* __restrict__ ab, int* __restrict__ kout) {
+                                                             double* __restrict__ Qg, double* __restrict__ ab,
+                                                             int* __restrict__ kout) {
     const double* __restrict__ T = blockIdx.x == 0 ? T0 : T1;
     Qg += (long)blockIdx.x * n * (LZ_MAX_K + 1);
     ab += blockIdx.x * 2 * LZ_MAX_K;
     kout += blockIdx.x;
     extern __shared__ double sm[];
     double* q = sm;                 // current Lanczos vector
-    double* w = sm + n;             // work vector
+    double* w = sm + n + LZ_TREG;   // work vector
     const int nch = n > LZ_THREADS / 2 ? 1 : LZ_THREADS / n;
-    double* pp = sm + 2 * n;        // partial products (nch > 1 only)
-    double* Q = qlds ? sm + 2 * n + (nch > 1 ? LZ_THREADS : 0) : Qg;
+    double* pp = w + n;             // partial products (nch > 1 only)
+    double* Q;
+    if constexpr (QLDS) Q = w + n + (nch > 1 ? LZ_THREADS : 0);
+    else Q = Qg;
     const long ldq = n;
     __shared__ double red[LZ_WAVES];
     __shared__ double h[LZ_MAX_K + 1];
     __shared__ double ta[LZ_MAX_K], tb[LZ_MAX_K];  // the tridiagonal so far
     __shared__ int first_hit;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x;
     double theta_prev = 0.0, tnorm = 0.0;
     const int clen = (n + nch - 1) / nch;
-
+    const int ci = tid % n, cc = tid / n, cl0 = cc * clen;
+    const bool chunked = nch > 1 && tid < n * nch;
+    const int cl1 = min(n, cl0 + clen);
     // deterministic start vector with no special structure
     double loc = 0.0;
     for (int i = tid; i < n; i += LZ_THREADS) {
@@ -79,19 +176,26 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_kernel(int n, const double
         q[i] = w[i] / nrm;
         Q[i] = q[i];
     }
+    for (int i = tid; i < LZ_TREG; i += LZ_THREADS) q[n + i] = 0.0;  // read past a last, shorter chunk
+    double treg[LZ_TREG];
+    if (chunked) {
+#pragma unroll
+        for (int u = 0; u < LZ_TREG; ++u) treg[u] = cl0 + u < cl1 ? T[ci + (long)(cl0 + u) * ldt] : 0.0;
+    }
     __syncthreads();
     double beta_prev = 0.0;
     int k = 0;
     for (int j = 0; j < kmax; ++j) {
         // w = T q
         if (nch > 1) {
-            if (tid < n * nch) {
-                const int i = tid % n, c = tid / n;
-                const int l0 = c * clen, l1 = min(n, l0 + clen);
-                const double* Ti = T + i;
+            if (chunked) {
                 double acc = 0.0;
+                // treg is zero past the chunk's end
+#pragma unroll
+                for (int u = 0; u < LZ_TREG; ++u) acc += treg[u] * q[cl0 + u];
+                const double* Ti = T + ci;
 #pragma unroll 8
-                for (int l = l0; l < l1; ++l) acc += Ti[(long)l * ldt] * q[l];
+                for (int l = cl0 + LZ_TREG; l < cl1; ++l) acc += Ti[(long)l * ldt] * q[l];
                 pp[tid] = acc;
             }
             __syncthreads();
@@ -121,18 +225,17 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_kernel(int n, const double
         __syncthreads();
         // full reorthogonalisation against q_0..q_j, twice
         for (int pass = 0; pass < 2; ++pass) {
-            for (int l = wv; l <= j; l += LZ_WAVES) {
-                double s = 0.0;
-                for (int i = lane; i < n; i += 64) s += Q[i + (long)l * ldq] * w[i];
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-                if (lane == 0) h[l] = s;
-            }
-            __syncthreads();
-            for (int i = tid; i < n; i += LZ_THREADS) {
-                double v = w[i];
-                for (int l = 0; l <= j; ++l) v -= h[l] * Q[i + (long)l * ldq];
-                w[i] = v;
+            lz_project(n, j, Q, ldq, w, h);
+            if (nch > 1) {
+                if (chunked) pp[tid] = lz_combine(ci, j, cc, nch, Q, ldq, h);
+                __syncthreads();
+                for (int i = tid; i < n; i += LZ_THREADS) {
+                    double v = 0.0;
+                    for (int c = 0; c < nch; ++c) v += pp[i + c * n];
+                    w[i] -= v;
+                }
+            } else {
+                for (int i = tid; i < n; i += LZ_THREADS) w[i] -= lz_combine(i, j, 0, 1, Q, ldq, h);
             }
             __syncthreads();
         }
@@ -154,34 +257,7 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_kernel(int n, const double
         // and the caller confirms the resulting step with a Cholesky test
         if (k >= 16 && (k & 7) == 0) {
             __syncthreads();
-            double lo = ta[0], hi = ta[0];
-            for (int i = 0; i < k; ++i) {
-                const double rr = (i > 0 ? fabs(tb[i - 1]) : 0.0) + (i + 1 < k ? fabs(tb[i]) : 0.0);
-                lo = fmin(lo, ta[i] - rr);
-                hi = fmax(hi, ta[i] + rr);
-            }
-            for (int round = 0; round < 6; ++round) {
-                const double step = (hi - lo) / (LZ_THREADS + 1);
-                const double x = lo + (tid + 1) * step;
-                int cnt = 0;
-                double dd = 1.0;
-                for (int i = 0; i < k; ++i) {
-                    const double bb = i > 0 ? tb[i - 1] * tb[i - 1] : 0.0;
-                    dd = ta[i] - x - (i > 0 ? bb / dd : 0.0);
-                    if (dd == 0.0) dd = -1e-300;
-                    if (dd < 0.0) ++cnt;
-                }
-                if (tid == 0) first_hit = LZ_THREADS;
-                __syncthreads();
-                if (cnt >= 1) atomicMin(&first_hit, tid);
-                __syncthreads();
-                const int t = first_hit;
-                __syncthreads();
-                const double nlo = lo + t * step, nhi = (t < LZ_THREADS) ? lo + (t + 1) * step : hi;
-                lo = nlo;
-                hi = nhi;
-            }
-            const double theta = 0.5 * (lo + hi);
+            const double theta = lz_smallest(ta, tb, k, &first_hit);
             const bool settled = k >= 24 && fabs(theta - theta_prev) <= 1e-10 * tnorm;
             theta_prev = theta;
             if (settled) break;
@@ -270,7 +346,7 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_orth_kernel(int n, int j, 
     __shared__ double h[LZ_MAX_K + 1];
     __shared__ double ta[LZ_MAX_K], tb[LZ_MAX_K];
     __shared__ int first_hit;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int tid = threadIdx.x;
     const double beta_prev = st[0], tnorm_prev = st[1], theta_prev = st[2];
     for (int i = tid; i < n; i += LZ_THREADS) {
         w[i] = W[i];
@@ -287,19 +363,8 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_orth_kernel(int n, int j, 
     }
     __syncthreads();
     for (int pass = 0; pass < 2; ++pass) {
-        for (int l = wv; l <= j; l += LZ_WAVES) {
-            double s = 0.0;
-            for (int i = lane; i < n; i += 64) s += Q[i + (long)l * n] * w[i];
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-            if (lane == 0) h[l] = s;
-        }
-        __syncthreads();
-        for (int i = tid; i < n; i += LZ_THREADS) {
-            double v = w[i];
-            for (int l = 0; l <= j; ++l) v -= h[l] * Q[i + (long)l * n];
-            w[i] = v;
-        }
+        lz_project(n, j, Q, n, w, h);
+        for (int i = tid; i < n; i += LZ_THREADS) w[i] -= lz_combine(i, j, 0, 1, Q, n, h);
         __syncthreads();
     }
     loc = 0.0;
@@ -329,34 +394,7 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_orth_kernel(int n, int j, 
             tb[j] = beta;
         }
         __syncthreads();
-        double lo = ta[0], hi = ta[0];
-        for (int i = 0; i < k; ++i) {
-            const double rr = (i > 0 ? fabs(tb[i - 1]) : 0.0) + (i + 1 < k ? fabs(tb[i]) : 0.0);
-            lo = fmin(lo, ta[i] - rr);
-            hi = fmax(hi, ta[i] + rr);
-        }
-        for (int round = 0; round < 6; ++round) {
-            const double step = (hi - lo) / (LZ_THREADS + 1);
-            const double x = lo + (tid + 1) * step;
-            int cnt = 0;
-            double dd = 1.0;
-            for (int i = 0; i < k; ++i) {
-                const double bb = i > 0 ? tb[i - 1] * tb[i - 1] : 0.0;
-                dd = ta[i] - x - (i > 0 ? bb / dd : 0.0);
-                if (dd == 0.0) dd = -1e-300;
-                if (dd < 0.0) ++cnt;
-            }
-            if (tid == 0) first_hit = LZ_THREADS;
-            __syncthreads();
-            if (cnt >= 1) atomicMin(&first_hit, tid);
-            __syncthreads();
-            const int t = first_hit;
-            __syncthreads();
-            const double nlo = lo + t * step, nhi = (t < LZ_THREADS) ? lo + (t + 1) * step : hi;
-            lo = nlo;
-            hi = nhi;
-        }
-        theta = 0.5 * (lo + hi);
+        theta = lz_smallest(ta, tb, k, &first_hit);
         const bool settled = k >= 24 && fabs(theta - theta_prev) <= 1e-10 * tnorm;
         if (settled) {
             if (tid == 0) done[b] = 1;
@@ -454,14 +492,18 @@ void lanczos_min_eig2(hipStream_t st, int n, const double* T0, const double* T1,
         }
     } else {
         const bool split = n <= LZ_THREADS / 2;
-        size_t shm = (2 * (size_t)n + (split ? LZ_THREADS : 0)) * sizeof(double);
+        size_t shm = (2 * (size_t)n + LZ_TREG + (split ? LZ_THREADS : 0)) * sizeof(double);
         const size_t qbytes = (size_t)n * (kmax + 1) * sizeof(double);
-        const size_t static_lds = (LZ_WAVES + LZ_MAX_K + 1) * sizeof(double) + 1024;  // red, h, slack
+        const size_t static_lds = (LZ_WAVES + LZ_MAX_K + 1) * sizeof(double) + 2048;  // red, h, the tridiagonal, slack
         const int qlds = shm + qbytes + static_lds <= lds_max ? 1 : 0;
         if (qlds) shm += qbytes;
         require(shm + static_lds <= lds_max, "lanczos: n too large for the workgroup's LDS");
-        hipLaunchKernelGGL(lanczos_kernel, dim3(runs), dim3(LZ_THREADS), shm, st, n, T0, T1 ? T1 : T0, ldt, kmax,
-                           w.Q.get(), qlds, w.ab.get(), w.kout.get());
+        if (qlds)
+            hipLaunchKernelGGL(lanczos_kernel<true>, dim3(runs), dim3(LZ_THREADS), shm, st, n, T0, T1 ? T1 : T0, ldt,
+                               kmax, w.Q.get(), w.ab.get(), w.kout.get());
+        else
+            hipLaunchKernelGGL(lanczos_kernel<false>, dim3(runs), dim3(LZ_THREADS), shm, st, n, T0, T1 ? T1 : T0, ldt,
+                               kmax, w.Q.get(), w.ab.get(), w.kout.get());
         WC_LAUNCH_CHECK();
     }
     WC_HIP(hipMemcpyAsync(w.pinned, w.ab.get(), 2 * LZ_MAX_K * runs * sizeof(double), hipMemcpyDeviceToHost, st));

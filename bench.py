@@ -97,14 +97,15 @@ def cpu_baseline(p, budget_s=15.0):
 
 
 def packed_source_digest():
-    """SHA-256 of the source text of the two packed-pass kernels and their launchers."""
+    """SHA-256 of the source text of the two packed-pass kernels, their launchers and the operator's last pass."""
     import hashlib
 
     src = open(KERNEL_SOURCE).read()
     a = src.index("constexpr int PK_ROWS")
     b = src.index("void packed_cols_partial(")
     b = src.index("\n}\n", b) + 3
-    return hashlib.sha256(src[a:b].encode()).hexdigest()
+    last = open(os.path.join(os.path.dirname(KERNEL_SOURCE), "dense_op.hip")).read()
+    return hashlib.sha256((src[a:b] + last).encode()).hexdigest()
 
 
 def gemm_source_digest():
@@ -507,7 +508,7 @@ def sensing_line(args, steps, warmup, with_cpu=True, with_mixed=True):
     avg_ms = kp["ms"] / max(kp["launches"], 1)
     bytes_per = kp["bytes"] / max(kp["launches"], 1)
     achieved = bytes_per / (avg_ms * 1e-3) / 1e9
-    kname = "packed_rows_kernel" if kcls == L.SDP_K_A_APPLY else "packed_cols_partial_kernel"
+    kname = "op_rows_kernel<double>" if kcls == L.SDP_K_A_APPLY else "packed_cols_partial_kernel"
 
     # tight loop of the operator at the final point
     N = ctx.aug_dim()
@@ -542,7 +543,8 @@ def sensing_line(args, steps, warmup, with_cpu=True, with_mixed=True):
         "newton_apply_loop": {"matvec_per_s": loop_rate, "calls": args.apply_loop},
         "mixed": mixed,
         "roofline": {
-            "kernel": ("packed_rows_kernel: A(M), one pass over the packed constraint rows"
+            "kernel": ("op_rows_kernel<double>: A(M), one pass over the packed constraint rows, and the "
+                       "off-diagonal products"
                        if kcls == L.SDP_K_A_APPLY else
                        "packed_cols_partial_kernel: A^T(u), one pass over the packed constraint rows"),
             "bound": "hbm",

@@ -466,7 +466,8 @@ sdp_status sdp_get_scaling(sdp_ctx* ctx, double* lam, double* V, int32_t* r, dou
  * recorded on the stream, which adds a few microseconds of dispatch per launch.
  */
 enum {
-    SDP_K_A_APPLY = 0,   /* A(M): packed dense rows times the weighted packed M */
+    SDP_K_A_APPLY = 0,   /* A(M): packed dense rows times the weighted packed M (the operator's
+                            launch also takes its off-diagonal products; their bytes are counted) */
     SDP_K_AT_APPLY = 1,  /* A^T(u): slab partial column sums of the packed rows */
     SDP_K_GEMM = 2,      /* every FP64 GEMM launch */
     SDP_K_NEWTON = 3,    /* a whole sdp_newton_apply */

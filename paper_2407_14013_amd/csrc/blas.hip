@@ -248,6 +248,16 @@ static void dgemm_launch(hipStream_t st, dim3 grid, bool big, int m, int n, int 
                            alpha, A, lda, B, ldb, beta, C, ldc, lo, sA, sB, sC, klast);
 }
 
+int dgemm_partials(hipStream_t st, int n, const double* A, long lda, const double* B, long ldb, double* ws,
+                   long ws_len) {
+    const SplitPlan sp = dgemm_split_plan(n, n, n, ws_len, GBM, GBN, GBK, GEMM_SPLITS, GEMM_SPLIT_TILES);
+    if (sp.splits < 2) return 0;
+    dgemm_launch<false, false>(st, dim3(cdiv(n, GBM), cdiv(n, GBN), sp.splits), false, n, n, sp.kc, 1.0, A, lda, B, ldb,
+                               0.0, ws, n, 0, (long)sp.kc * lda, sp.kc, (long)n * n, sp.klast);
+    WC_LAUNCH_CHECK();
+    return sp.splits;
+}
+
 void dgemm(hipStream_t st, bool ta, bool tb, int m, int n, int k, double alpha, const double* A, long lda,
            const double* B, long ldb, double beta, double* C, long ldc, bool lower_only, int batch, long sA, long sB,
            long sC, double* ws, long ws_len) {
@@ -271,7 +281,6 @@ void dgemm(hipStream_t st, bool ta, bool tb, int m, int n, int k, double alpha, 
         return;
     }
     int lo = lower_only ? 1 : 0;
-    const long tiles = (long)cdiv(m, GBM) * cdiv(n, GBN);
     // kk: the K of every z-slice but a split launch's last (klast); big: 128 x 128 tiles
     auto launch = [&](dim3 grid, bool big, int kk, double al, double be, double* Cx, long ldx, long sa, long sb,
                       long sc, int klast) {

@@ -92,6 +92,11 @@ void dgemm(hipStream_t st, bool ta, bool tb, int m, int n, int k, double alpha, 
            const double* B, long ldb, double beta, double* C, long ldc, bool lower_only = false, int batch = 1,
            long sA = 0, long sB = 0, long sC = 0, double* ws = nullptr, long ws_len = 0);
 long dgemm_splitk_ws();
+// The split-K partial products of A B (n x n, plain operands) into ws (ld n,
+// n * n apart) as dgemm would form them, without the sum; returns their number,
+// 0 when dgemm would not split (nothing launched).
+int dgemm_partials(hipStream_t st, int n, const double* A, long lda, const double* B, long ldb, double* ws,
+                   long ws_len);
 // C = A B for a product known to be symmetric (n x n, op = identity): the
 // entries with row >= col are written, others may or may not be.  Computes
 // only the lower triangle's tiles when dgemm_lower_pays(n) (large n), the

@@ -695,43 +695,9 @@ void to_f32(hipStream_t st, long count, const double* x, float* y) {
     WC_LAUNCH_CHECK();
 }
 
-// ---- packed constraint passes over FP32 rows ---------------------------------------------
-constexpr int PF_ROWS = 4;     // rows per workgroup of the A(M) pass
+// ---- packed constraint pass over FP32 rows ---------------------------------------------
 constexpr int PF_SLAB = 64;    // row slab of the A^T(u) pass
 constexpr int PF_UNROLL = 8;   // rows in flight per thread in the A^T(u) pass
-
-__global__ __launch_bounds__(256) void packed_rows_f32_kernel(int m, int k4, const float* __restrict__ P, long ldp,
-                                                              const float* __restrict__ x, double* __restrict__ y,
-                                                              double alpha, double beta) {
-    __shared__ double sh[4];
-    const int row0 = blockIdx.x * PF_ROWS;
-    double acc[PF_ROWS];
-#pragma unroll
-    for (int r = 0; r < PF_ROWS; ++r) acc[r] = 0.0;
-    const lf4* x4 = reinterpret_cast<const lf4*>(x);
-    const lf4* arow[PF_ROWS];
-#pragma unroll
-    for (int r = 0; r < PF_ROWS; ++r) {
-        const int row = row0 + r < m ? row0 + r : m - 1;
-        arow[r] = reinterpret_cast<const lf4*>(P + (long)row * ldp);
-    }
-    for (int c = threadIdx.x; c < k4; c += 256) {
-        const lf4 xv = x4[c];
-#pragma unroll
-        for (int r = 0; r < PF_ROWS; ++r) {
-            const lf4 av = __builtin_nontemporal_load(&arow[r][c]);
-            acc[r] += (double)av.x * xv.x + (double)av.y * xv.y + (double)av.z * xv.z + (double)av.w * xv.w;
-        }
-    }
-#pragma unroll
-    for (int r = 0; r < PF_ROWS; ++r) {
-        const double s = lp_block_sum<256>(acc[r], sh);
-        if (threadIdx.x == 0 && row0 + r < m) {
-            const double v = alpha * s;
-            y[row0 + r] = (beta == 0.0) ? v : v + beta * y[row0 + r];
-        }
-    }
-}
 
 __global__ __launch_bounds__(256) void packed_cols_partial_f32_kernel(int m, int k4, const float* __restrict__ P,
                                                                       long ldp, const double* __restrict__ x,
@@ -770,16 +736,6 @@ __global__ __launch_bounds__(256) void packed_cols_partial_f32_kernel(int m, int
 }
 
 int packed_cols_parts_f32(int m) { return cdiv(m, PF_SLAB); }
-
-void packed_rows_f32(hipStream_t st, int m, int k, const float* P, long ldp, const float* x, double* y,
-                     double alpha, double beta) {
-    if (m <= 0) return;
-    require(ldp % 4 == 0, "packed_rows_f32: row pitch must be a multiple of 4");
-    const int k4 = static_cast<int>(round_up(k, 4) / 4);
-    hipLaunchKernelGGL(packed_rows_f32_kernel, dim3(cdiv(m, PF_ROWS)), dim3(256), 0, st, m, k4, P, ldp, x, y, alpha,
-                       beta);
-    WC_LAUNCH_CHECK();
-}
 
 void packed_cols_partial_f32(hipStream_t st, int m, int k, const float* P, long ldp, const double* x, double* part) {
     if (k <= 0 || m <= 0) return;

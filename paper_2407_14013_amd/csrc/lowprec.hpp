@@ -46,15 +46,10 @@ void to_lowp(hipStream_t st, Lp p, int rows, int cols, const double* A, long lda
 // y = x rounded to FP32 (count elements).
 void to_f32(hipStream_t st, long count, const double* x, float* y);
 
-// Packed constraint passes over FP32 rows P (m x ldp row-major, ldp a multiple
-// of 4, zero padded), accumulated in FP64:
-//   packed_rows_f32: y = alpha P x + beta y with x FP32, readable and zero
-//     padded up to round_up(k, 4);
-//   packed_cols_partial_f32: packed_cols_parts_f32(m) slab partial sums of
-//     P^T x into `part` with row pitch round_up(k, 4).
+// Packed constraint pass over FP32 rows P (m x ldp row-major, ldp a multiple of
+// 4, zero padded), accumulated in FP64: packed_cols_parts_f32(m) slab partial
+// sums of P^T x into `part` with row pitch round_up(k, 4).
 int packed_cols_parts_f32(int m);
-void packed_rows_f32(hipStream_t st, int m, int k, const float* P, long ldp, const float* x, double* y,
-                     double alpha, double beta);
 void packed_cols_partial_f32(hipStream_t st, int m, int k, const float* P, long ldp, const double* x, double* part);
 
 // Packed weights of a symmetric M in FP32 (mw[p] = M_jj, or M_jk + M_kj off

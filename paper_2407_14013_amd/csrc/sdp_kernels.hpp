@@ -69,7 +69,6 @@ void neg_div(hipStream_t st, int d, const double* qc, const double* sig, double*
 void corrector_h(hipStream_t st, int n, const double* Pm, const double* dv, double smu, double* H);
 void rho_bottom(hipStream_t st, int d, const double* h, const double* a, const double* sig, double t2,
                 const double* zv, double* out);
-void aq_bottom(hipStream_t st, int d, const double* a, const double* sig, double t2, const double* v, double* out);
 // Preconditioner top-block updates: z1 = (f - tm) / beta (and rho_u = f - tm - beta z1 when rho is
 // given); the refinement's final correction z[:m] += dz, z[m:m+d] = a + b
 void precond_top(hipStream_t st, long m, double ib, double beta, const double* f, const double* tm, double* z1,

@@ -7,6 +7,7 @@
 #include <cmath>
 #include <limits>
 
+#include "dense_op.hpp"
 #include "lanczos.hpp"
 #include "lp_kernels.hpp"
 #include "sdp_kernels.hpp"
@@ -89,13 +90,18 @@ static void a_apply(sdp_ctx* c, const double* M, double* out, double alpha, doub
     }
 }
 
+// Dense rows: the slab partial sums of A^T(u)'s packed entries into gpart
+static void at_partials(sdp_ctx* c, const double* u) {
+    hipEvent_t e0, e1;
+    prof_kernel_events(c, SDP_K_AT_APPLY, &e0, &e1);
+    packed_cols_partial(c->st, c->m, static_cast<int>(c->N2), c->P, c->ldP, u, c->gpart, e0, e1);
+    prof_kernel_done(c, SDP_K_AT_APPLY, e0, e1, 8.0 * c->m * c->N2 + 8.0 * c->m);
+}
+
 // Y = A^T(u), full symmetric n x n
 static void at_apply(sdp_ctx* c, const double* u, double* Y) {
     if (c->kind == SDP_A_DENSE) {
-        hipEvent_t e0, e1;
-        prof_kernel_events(c, SDP_K_AT_APPLY, &e0, &e1);
-        packed_cols_partial(c->st, c->m, static_cast<int>(c->N2), c->P, c->ldP, u, c->gpart, e0, e1);
-        prof_kernel_done(c, SDP_K_AT_APPLY, e0, e1, 8.0 * c->m * c->N2 + 8.0 * c->m);
+        at_partials(c, u);
         at_reduce_unpack(c->st, c->N2, packed_cols_parts(c->m), c->gpart, round_up(c->N2, 2), c->pj, c->pk, Y, c->n);
     } else if (c->kind == SDP_A_ENTRY) {
         fill(c->st, (long)c->n * c->n, Y, 0.0);
@@ -847,6 +853,43 @@ static void lp_operator(sdp_ctx* c, const double* u, const double* v, double* ou
     lp_b(c->st, m, c->lrptr, c->lrcol, c->lrval, c->lz, out, 1.0, 1.0);
 }
 
+// The operator's SDP part for dense rows: Y = A^T(u), the packed weights of
+// E Y E, then one pass with the off-diagonal blocks (see dense_op.hip).
+static void dense_operator(sdp_ctx* c, const double* u, const double* v, double* out) {
+    const int n = c->n, m = c->m;
+    hipStream_t st = c->st;
+    const double sw_bytes = 8.0 * 3.0 * (double)n * n;
+    hipEvent_t es, e0, e1;
+    if (n <= DENSE_MID_N) {
+        at_partials(c, u);
+        prof_begin(c, SDP_K_SANDWICH, &es);
+        dense_mid(st, n, c->N2, c->ldP, packed_cols_parts(m), c->gpart, round_up(c->N2, 2), c->pj, c->pk, c->E, c->mw);
+        prof_end(c, SDP_K_SANDWICH, es, sw_bytes);
+    } else {
+        at_apply(c, u, c->Y);
+        prof_begin(c, SDP_K_SANDWICH, &es);
+        gemm(c, false, false, n, n, n, 1.0, c->Y, n, c->E, n, 0.0, c->T1, n);
+        prof_end(c, SDP_K_SANDWICH, es, sw_bytes);
+        // E (Y E) is symmetric: at large n only its lower triangle is computed
+        const bool lower = dgemm_lower_pays(n);
+        const int cls = lower ? SDP_K_SANDWICH_LOWER : SDP_K_SANDWICH;
+        prof_begin(c, cls, &es);
+        const int splits = dgemm_partials(st, n, c->E, n, c->T1, n, c->gemm_ws, static_cast<long>(c->gemm_ws.n));
+        if (splits == 0) gemm_sym(c, c->E, c->T1, c->Mm);
+        prof_end(c, cls, es, lower ? 4.0 * (double)n * n : sw_bytes);
+        if (splits > 0) {
+            reduce_pack(st, n, c->N2, c->ldP, splits, c->gemm_ws, c->pj, c->pk, c->mw);
+        } else {
+            sym_finish(c, 0, nullptr, c->Mm);
+            pack_weighted(st, n, c->N2, c->ldP, c->Mm, n, c->pj, c->pk, c->mw);
+        }
+    }
+    prof_kernel_events(c, SDP_K_A_APPLY, &e0, &e1);
+    op_rows<double>(st, m, c->N2, c->P, c->ldP, c->mw, c->d, c->AQ, c->dmaxp, c->AQt, c->ldAQt, u, v, c->sig,
+                    c->tau * c->tau, out, e0, e1);
+    prof_kernel_done(c, SDP_K_A_APPLY, e0, e1, 8.0 * m * c->N2 + 8.0 * c->N2 + 8.0 * m + 16.0 * m * c->d);  // P, x, y, AQ both ways
+}
+
 void newton_apply(sdp_ctx* c, const double* in, double* out) {
     ensure_scaling(c);
     const int n = c->n, m = c->m, r = c->r;
@@ -875,6 +918,13 @@ void newton_apply(sdp_ctx* c, const double* in, double* out) {
         entry_yq(st, n, r, c->rptr, c->rcol, c->ridx, u, c->Gw, n, c->YQ);
         gemm(c, true, false, n, r, n, 1.0, c->Gw, n, c->YQ, n, 0.0, c->F, n);
         f_to_v(st, n, r, c->F, n, v, c->sig, c->tau * c->tau, out + m);
+        lp_operator(c, u, v, out);
+        prof_end(c, SDP_K_NEWTON, e, 0.0);
+        c->matvecs += 1;
+        return;
+    }
+    if (c->kind == SDP_A_DENSE) {
+        dense_operator(c, u, v, out);
         lp_operator(c, u, v, out);
         prof_end(c, SDP_K_NEWTON, e, 0.0);
         c->matvecs += 1;
@@ -949,12 +999,9 @@ void newton_apply_lowp(sdp_ctx* c, const double* in, double* out) {
                             nullptr, n, c->Ylp);
         sandwich_lp(c, tout, LpOut::F64);
         pack_weighted_f32(st, c->N2, c->ldP, c->Mm, n, c->pj, c->pk, c->mw32);
-        packed_rows_f32(st, m, static_cast<int>(c->N2), c->P32, c->ldP, c->mw32, out, 1.0, 0.0);
-        // top += AQ v (v staged in an aligned, zero-padded buffer); bottom = AQ^T u - tau^2 Sigma v
-        copy(st, d, v, c->td2);
-        gemv_rows(st, m, d, c->AQ, c->dmaxp, c->td2, out, 1.0, 1.0);
-        gemv_rows(st, d, m, c->AQt, c->ldAQt, u, c->td3, 1.0, 0.0);
-        aq_bottom(st, d, c->td3, c->sig, c->tau * c->tau, v, out + m);
+        // with top += AQ v and bottom = AQ^T u - tau^2 Sigma v in the same pass
+        op_rows<float>(st, m, c->N2, c->P32, c->ldP, c->mw32, d, c->AQ, c->dmaxp, c->AQt, c->ldAQt, u, v, c->sig,
+                       c->tau * c->tau, out);
     } else {
         // Only the m sampled entries of E Y E + sym(U Q^T) are needed: Y goes
         // straight into its low-precision copy, E (Y E) is written in FP32 over
@@ -1065,6 +1112,18 @@ static void precond_apply(sdp_ctx* c, const double* rv, double* z) {
     const double* f = rv;
     const double* h = rv + m;
     double* z1 = z;
+    if (c->kind == SDP_A_DENSE && c->ell == 0) {
+        // the same steps with the vector work inside the passes over AQ, and
+        // rho_v - AQ^T rho_u / beta formed at once
+        const double ib = 1.0 / c->beta;
+        precond_down(st, m, d, c->AQt, c->ldAQt, f, h, ib, c->td);
+        symv(st, d, c->Cinv, c->dmaxp, c->td, c->td2, -1.0, 0.0, c->sy_ws);
+        precond_up(st, m, d, c->AQ, c->dmaxp, c->td2, f, ib, c->beta, z1, c->rho);
+        precond_down2(st, m, d, c->AQt, c->ldAQt, z1, c->rho, h, c->sig, c->tau * c->tau, c->td2, ib, c->td);
+        symv(st, d, c->Cinv, c->dmaxp, c->td, c->td3, -1.0, 0.0, c->sy_ws);
+        precond_up2(st, m, d, c->AQ, c->dmaxp, c->td2, c->td3, c->rho, ib, z1, z + m);
+        return;
+    }
     // rho = rv - P z:  rho_u = f - tm - beta z1 (formed with z1),  rho_v = h - AQ^T z1 + tau^2 Sigma zv
     precond_block(c, f, h, z1, c->td2, c->rho);
     aqt_mul(c, z1, c->td3, 1.0, 0.0);                                      // td3 = AQ^T z1

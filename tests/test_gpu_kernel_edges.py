@@ -11,6 +11,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 import workloads  # noqa: E402
+from oracle import nt, reform as rf  # noqa: E402
 from paper_2407_14013_amd import Context, batched  # noqa: E402
 from paper_2407_14013_amd import linalg as la  # noqa: E402
 
@@ -57,3 +58,45 @@ def test_batched_edges_match_single_solver(n, r, rank_max, prec):
     Xstar = p["U"] @ p["U"].T
     for Y in (Xs[0], X):
         assert np.linalg.norm(Y.cpu().numpy() - Xstar) <= 1e-6 * np.linalg.norm(Xstar)
+
+
+def scaled_point(n, seed):
+    X, S = workloads.random_pd_pair(n, seed=seed, spread=0.5)
+    G, _, _ = nt.nt_factor(X, S)
+    return X, S, G @ G.T
+
+
+# dense rows: the operator's single-workgroup middle (n <= 64, tile edges) and
+# the split-K one, odd m and d, one constraint, vectors that are only 8-byte
+# aligned.  1e-10 of the largest entry, the bound of the operator's other
+# checks: FP64 sums of length n (n + 1) / 2 <= 2 211 and eigenvectors of
+# well-separated spectra.
+@pytest.mark.parametrize("n, m", [(2, 1), (3, 4), (15, 37), (16, 64), (17, 101), (48, 129), (63, 300), (64, 257),
+                                  (65, 301), (66, 128), (97, 255)])
+@pytest.mark.parametrize("rank", [1, 2])
+def test_dense_operator_and_preconditioner_edges(n, m, rank):
+    if rank >= n:
+        pytest.skip("the rank parameter is below n")
+    p = workloads.generic_sensing(n, m, seed=n + m)
+    X, S, W = scaled_point(n, seed=n)
+    sp = rf.eig_split(W, rank_fixed=rank)
+    sig, E = rf.sigma_diag(sp), rf.e_matrix(sp)
+    N = m + rf.dim_d(n, rank)
+    x = np.random.default_rng(m).standard_normal(N)
+    t, b = rf.aug_apply(p, sp, E, sig, x[:m], x[m:])
+    ref = np.concatenate([t, b])
+    for prec, tol in ((0, 1e-10), (1, 1e-5)):  # FP32: E Y E and the rows carry 24 bits, sums of length n in FP32
+        with Context(p, rank_fixed=rank, inner_prec=prec) as ctx:
+            ctx.set_point(*(torch.from_numpy(a).cuda() for a in (X, np.zeros(m), S)))
+            assert ctx.aug_dim() == N
+            for shift in (0, 1):
+                buf = torch.zeros(N + shift, dtype=torch.float64, device="cuda")
+                buf[shift:] = torch.from_numpy(x)
+                out = torch.full((N + shift,), np.nan, dtype=torch.float64, device="cuda")
+                got = ctx.newton_apply(buf[shift:], out[shift:], prec=prec if prec else None).cpu().numpy()
+                assert np.abs(got - ref).max() <= tol * np.abs(ref).max(), (prec, shift)
+            if prec == 0:
+                # backward error of P z = x with the oracle's P
+                P = rf.precond_matrix(rf.aq_matrix(p, sp), sp, sig, ctx.get_scaling()["beta"])
+                z = ctx.precond_apply(torch.from_numpy(x).cuda()).cpu().numpy()
+                assert np.abs(P @ z - x).max() <= 1e-9 * np.abs(P).sum(1).max() * np.abs(z).max()

@@ -459,7 +459,7 @@ __global__ __launch_bounds__(256) void dgemm_thin_t_kernel(int M, int N, int K, 
 #pragma unroll
         for (int j = 0; j < NM; ++j) acc[t][j] = 0.0;
     int k = k0 + lane;
-    if constexpr (NM <= 4) {
+    if constexpr (NM <= 8) {
         // two steps' loads of A and B issued before their products (B's column
         // index clamped to a valid one, the value used only for j < N); the
         // guarded loop below waits for every load
@@ -638,6 +638,9 @@ bool dgemm_thin(hipStream_t st, bool ta, int m, int n, int k, double alpha, cons
     } else {
         if (n <= 4)
             hipLaunchKernelGGL(dgemm_thin_t_kernel<4>, dim3(cdiv(m, 4)), dim3(256), 0, st, m, n, k, alpha, A, lda, B,
+                               ldb, beta, C, ldc);
+        else if (n <= 8)
+            hipLaunchKernelGGL(dgemm_thin_t_kernel<8>, dim3(cdiv(m, 4)), dim3(256), 0, st, m, n, k, alpha, A, lda, B,
                                ldb, beta, C, ldc);
         else
             hipLaunchKernelGGL(dgemm_thin_t_kernel<THIN_N>, dim3(cdiv(m, 4)), dim3(256), 0, st, m, n, k, alpha, A, lda,

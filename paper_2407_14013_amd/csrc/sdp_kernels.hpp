@@ -46,11 +46,7 @@ void sparse_aq(hipStream_t st, int m, int n, int rk, const int* ptr, const int* 
 void sparse_aq_apply(hipStream_t st, int m, int n, int rk, const int* ptr, const int* row, const int* col,
                      const double* val, const double* U, const double* Q, long ldq, double* out, double alpha,
                      double beta);
-// Entry-sampling script-A script-Q products and Schur-complement blocks (implicit, see sdp_kernels.hip).
-void aq_entry_apply(hipStream_t st, int m, int n, int r, const int* jk, const double* U, const double* Q, long ldq,
-                    double* out, double alpha, double beta);
-void entry_yq(hipStream_t st, int n, int r, const int* rptr, const int* rcol, const int* ridx, const double* u,
-              const double* Q, long ldq, double* YQ);
+// Entry-sampling Schur-complement blocks (implicit, see sdp_kernels.hip).
 void entry_gram_block(hipStream_t st, int n, int b, int b2, const int* rptr, const int* rcol, const double* Q, long ldq,
                       double* B, long ldb);
 // Sampled A(E Y E) for entry sampling: slot values of the sliced pattern,

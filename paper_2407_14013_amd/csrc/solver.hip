@@ -8,6 +8,7 @@
 #include <limits>
 
 #include "dense_op.hpp"
+#include "entry_op.hpp"
 #include "lanczos.hpp"
 #include "lp_kernels.hpp"
 #include "sdp_kernels.hpp"
@@ -155,8 +156,8 @@ static void alloc_work(sdp_ctx* c) {
     c->sig.alloc(c->dmaxp);
     c->Hm.alloc((long)n * c->rmax);
     c->U.alloc((long)n * c->rmax);
-    c->YQ.alloc((long)n * c->rmax);
-    c->F.alloc((long)n * c->rmax);
+    c->YQ.alloc(2L * n * c->rmax);  // two vectors side by side (entry sampling)
+    c->F.alloc(2L * n * c->rmax);
     if (c->kind != SDP_A_ENTRY) {  // dense and sparse rows: script-A script-Q explicit (for C) ...
         c->AQ.alloc((long)m * c->dmaxp);
         if (c->kind == SDP_A_DENSE) {  // ... and, for dense rows, row-major (AQ)^T for the preconditioner
@@ -853,6 +854,16 @@ static void lp_operator(sdp_ctx* c, const double* u, const double* v, double* ou
     lp_b(c->st, m, c->lrptr, c->lrcol, c->lrval, c->lz, out, 1.0, 1.0);
 }
 
+// lp: with the LP columns in T (the preconditioner; the operator has its own LP part)
+static EntryAq entry_aq_args(sdp_ctx* c, bool lp = false) {
+    EntryAq q{c->n,  c->m,   c->r,  c->jk, c->rptr, c->rcol, c->ridx,
+              c->Gw, c->sig, c->Hm, c->U,  c->YQ,   c->F,    c->thin_ws, static_cast<long>(c->thin_ws.n), {}};
+    if (lp && c->t > 0)
+        q.lp = EntryLp{c->t,     c->Tl,    c->lcptr, c->lcrow, c->lrptr,
+                       c->lrcol, c->posl, c->lcval, c->lrval};
+    return q;
+}
+
 // The operator's SDP part for dense rows: Y = A^T(u), the packed weights of
 // E Y E, then one pass with the off-diagonal blocks (see dense_op.hip).
 static void dense_operator(sdp_ctx* c, const double* u, const double* v, double* out) {
@@ -912,12 +923,9 @@ void newton_apply(sdp_ctx* c, const double* in, double* out) {
         sampled_dots(st, n, c->dptr, c->dpart, c->didx, c->E, n, c->T1, n, out);
         prof_end(c, SDP_K_SAMPLED_DOTS, es, 16.0 * nn + 16.0 * m);
         // top += script-A script-Q v;  bottom = (script-A script-Q)^T u - tau^2 Sigma v
-        v_to_h(st, n, r, v, c->Hm);
-        gemm(c, false, false, n, r, n, 1.0, c->Gw, n, c->Hm, n, 0.0, c->U, n);
-        aq_entry_apply(st, m, n, r, c->jk, c->U, c->Gw, n, out, 1.0, 1.0);
-        entry_yq(st, n, r, c->rptr, c->rcol, c->ridx, u, c->Gw, n, c->YQ);
-        gemm(c, true, false, n, r, n, 1.0, c->Gw, n, c->YQ, n, 0.0, c->F, n);
-        f_to_v(st, n, r, c->F, n, v, c->sig, c->tau * c->tau, out + m);
+        const EntryAq q = entry_aq_args(c);
+        entry_aq_op(st, q, v, nullptr, false, 0, out);
+        entry_aqt(st, q, u, 1.0, nullptr, 0.0, nullptr, -(c->tau * c->tau), v, out + m);
         lp_operator(c, u, v, out);
         prof_end(c, SDP_K_NEWTON, e, 0.0);
         c->matvecs += 1;
@@ -941,8 +949,22 @@ void newton_apply(sdp_ctx* c, const double* in, double* out) {
     // E (Y E) is symmetric: at large n only its lower triangle is computed
     const bool lower = dgemm_lower_pays(n);
     prof_begin(c, lower ? SDP_K_SANDWICH_LOWER : SDP_K_SANDWICH, &es);
-    gemm_sym(c, c->E, c->T1, c->Mm);
+    // entry sampling reads E Y E at the sampled pairs only, so split-K partial
+    // products need no sum and a lower triangle no mirror
+    const bool entry = c->kind == SDP_A_ENTRY;
+    const int splits =
+        entry ? dgemm_partials(st, n, c->E, n, c->T1, n, c->gemm_ws, static_cast<long>(c->gemm_ws.n)) : 0;
+    if (splits == 0) gemm_sym(c, c->E, c->T1, c->Mm);
     prof_end(c, lower ? SDP_K_SANDWICH_LOWER : SDP_K_SANDWICH, es, lower ? 8.0 * 0.5 * nn : sw_bytes);
+    if (entry) {
+        const EntryAq q = entry_aq_args(c);
+        entry_aq_op(st, q, v, splits > 0 ? c->gemm_ws.get() : c->Mm.get(), lower, splits, out);
+        entry_aqt(st, q, u, 1.0, nullptr, 0.0, nullptr, -(c->tau * c->tau), v, out + m);
+        lp_operator(c, u, v, out);
+        prof_end(c, SDP_K_NEWTON, e, 0.0);
+        c->matvecs += 1;
+        return;
+    }
     // Mm += sym(U Q^T) (after the products, which then need not read Mm)
     v_to_h(st, n, r, v, c->Hm);
     gemm(c, false, false, n, r, n, 1.0, c->Gw, n, c->Hm, n, 0.0, c->U, n);
@@ -988,7 +1010,7 @@ static void sandwich_lp(sdp_ctx* c, LpOut tout, LpOut mout) {
 void newton_apply_lowp(sdp_ctx* c, const double* in, double* out) {
     ensure_scaling(c);
     require(c->lowp, "the context was set up with FP64 inner precision");
-    const int n = c->n, m = c->m, r = c->r, d = c->d;
+    const int n = c->n, m = c->m, d = c->d;
     hipStream_t st = c->st;
     const double* u = in;
     const double* v = in + m;
@@ -1024,21 +1046,19 @@ void newton_apply_lowp(sdp_ctx* c, const double* in, double* out) {
         prof_end(c, SDP_K_SANDWICH, es, bytes + 2.0 * nn);
         entry_gather_f32(st, m, c->jk, Mf, n, out, 1.0, 0.0);
         // top += script-A script-Q v;  bottom = (script-A script-Q)^T u - tau^2 Sigma v
-        v_to_h(st, n, r, v, c->Hm);
-        gemm(c, false, false, n, r, n, 1.0, c->Gw, n, c->Hm, n, 0.0, c->U, n);
-        aq_entry_apply(st, m, n, r, c->jk, c->U, c->Gw, n, out, 1.0, 1.0);
-        entry_yq(st, n, r, c->rptr, c->rcol, c->ridx, u, c->Gw, n, c->YQ);
-        gemm(c, true, false, n, r, n, 1.0, c->Gw, n, c->YQ, n, 0.0, c->F, n);
-        f_to_v(st, n, r, c->F, n, v, c->sig, c->tau * c->tau, out + m);
+        const EntryAq q = entry_aq_args(c);
+        entry_aq_op(st, q, v, nullptr, false, 0, out);
+        entry_aqt(st, q, u, 1.0, nullptr, 0.0, nullptr, -(c->tau * c->tau), v, out + m);
     }
     lp_operator(c, u, v, out);
     c->lp_matvecs += 1;
 }
 
-// out = alpha (script-A script-Q) v + beta out (m).  Dense A: the explicit
-// matrix (v in an aligned, zero-padded buffer).  Entry sampling and sparse
-// rows: U = G_w H(v), then one closed-form gather per constraint (O(nnz r)
-// instead of a pass over the m x d rows).  Uses Hm and U.
+// out = alpha (script-A script-Q) v + beta out (m), for dense rows (the explicit
+// matrix; v in an aligned, zero-padded buffer) and sparse rows (U = G_w H(v),
+// then one closed-form gather per constraint, O(nnz r) instead of a pass over
+// the m x d rows).  Uses Hm and U.  Entry sampling has its own products
+// (entry_op.hip).
 static void aq_mul(sdp_ctx* c, const double* v, double* out, double alpha, double beta) {
     const int n = c->n, r = c->r;
     if (c->kind == SDP_A_DENSE) {
@@ -1046,21 +1066,16 @@ static void aq_mul(sdp_ctx* c, const double* v, double* out, double alpha, doubl
     } else {
         v_to_h(c->st, n, r, v, c->Hm);
         gemm(c, false, false, n, r, n, 1.0, c->Gw, n, c->Hm, n, 0.0, c->U, n);
-        if (c->kind == SDP_A_ENTRY)
-            aq_entry_apply(c->st, c->m, n, r, c->jk, c->U, c->Gw, n, out, alpha, beta);
-        else
-            sparse_aq_apply(c->st, c->m, n, r, c->spptr, c->sprow, c->spcol, c->spval, c->U, c->Gw, n, out, alpha,
-                            beta);
+        sparse_aq_apply(c->st, c->m, n, r, c->spptr, c->sprow, c->spcol, c->spval, c->U, c->Gw, n, out, alpha, beta);
     }
     // the LP columns B[:, T]
     if (c->t > 0) lp_b_top(c->st, c->m, c->lrptr, c->lrcol, c->lrval, c->posl, v + c->d, out, alpha);
 }
 
 // out = alpha (script-A script-Q)^T u + beta out (+ add, may be null; d plus
-// the LP coordinates in T): F = G_w^T (A^T(u) Q) read in v-coordinates and
-// scaled into out in one pass.  Entry sampling forms A^T(u) Q with the sparse
-// product row by row; sparse rows scatter A^T(u) into Y and multiply.  Uses
-// YQ, F (and Y for sparse rows).
+// the LP coordinates in T), for dense and sparse rows.  Sparse rows: A^T(u)
+// scattered into Y, F = G_w^T (Y Q) read in v-coordinates and scaled into out in
+// one pass.  Uses YQ, F and Y.
 static void aqt_mul(sdp_ctx* c, const double* u, double* out, double alpha, double beta,
                     const double* add = nullptr) {
     const int n = c->n, r = c->r;
@@ -1068,12 +1083,8 @@ static void aqt_mul(sdp_ctx* c, const double* u, double* out, double alpha, doub
         gemv_rows(c->st, c->d, c->m, c->AQt, c->ldAQt, u, out, alpha, beta);
         if (add) axpby(c->st, c->d, 1.0, add, 1.0, out);
     } else {
-        if (c->kind == SDP_A_ENTRY) {
-            entry_yq(c->st, n, r, c->rptr, c->rcol, c->ridx, u, c->Gw, n, c->YQ);
-        } else {
-            at_apply(c, u, c->Y);
-            gemm(c, false, false, n, r, n, 1.0, c->Y, n, c->Gw, n, 0.0, c->YQ, n);
-        }
+        at_apply(c, u, c->Y);
+        gemm(c, false, false, n, r, n, 1.0, c->Y, n, c->Gw, n, 0.0, c->YQ, n);
         gemm(c, true, false, n, r, n, 1.0, c->Gw, n, c->YQ, n, 0.0, c->F, n);
         f_to_v_axpby(c->st, n, r, c->F, n, alpha, beta, add, out);
     }
@@ -1122,6 +1133,17 @@ static void precond_apply(sdp_ctx* c, const double* rv, double* z) {
         precond_down2(st, m, d, c->AQt, c->ldAQt, z1, c->rho, h, c->sig, c->tau * c->tau, c->td2, ib, c->td);
         symv(st, d, c->Cinv, c->dmaxp, c->td, c->td3, -1.0, 0.0, c->sy_ws);
         precond_up2(st, m, d, c->AQ, c->dmaxp, c->td2, c->td3, c->rho, ib, z1, z + m);
+        return;
+    }
+    if (c->kind == SDP_A_ENTRY) {
+        const double ib = 1.0 / c->beta;
+        const EntryAq q = entry_aq_args(c, true);
+        entry_aqt(st, q, f, -ib, nullptr, 0.0, h, 0.0, nullptr, c->td);
+        symv(st, d, c->Cinv, c->dmaxp, c->td, c->td2, -1.0, 0.0, c->sy_ws);
+        entry_aq_up(st, q, c->td2, f, ib, c->beta, z1, c->rho);
+        entry_aqt(st, q, z1, -1.0, c->rho, -ib, h, c->tau * c->tau, c->td2, c->td);
+        symv(st, d, c->Cinv, c->dmaxp, c->td, c->td3, -1.0, 0.0, c->sy_ws);
+        entry_aq_up2(st, q, c->td3, c->rho, ib, z1, c->td2, z + m);
         return;
     }
     // rho = rv - P z:  rho_u = f - tm - beta z1 (formed with z1),  rho_v = h - AQ^T z1 + tau^2 Sigma zv

@@ -100,3 +100,49 @@ def test_dense_operator_and_preconditioner_edges(n, m, rank):
                 P = rf.precond_matrix(rf.aq_matrix(p, sp), sp, sig, ctx.get_scaling()["beta"])
                 z = ctx.precond_apply(torch.from_numpy(x).cuda()).cpu().numpy()
                 assert np.abs(P @ z - x).max() <= 1e-9 * np.abs(P).sum(1).max() * np.abs(z).max()
+
+
+# entry sampling: rows with no sampled entry, one pair, r at 4 | 5 and 16 | 17
+# columns per launch, n at 1024 and n r at 8192 (the latency-bound forms' range),
+# with and without the LP block.  The split is the GPU's own, so what is
+# compared is sums of length n: 1e-10 of the largest entry as above.
+@pytest.mark.parametrize("n, m, rank, lp", [(2, 1, 1, True), (5, 3, 2, False), (33, 200, 3, True), (64, 500, 4, True),
+                                            (65, 500, 5, True), (130, 2000, 16, False), (130, 900, 17, True),
+                                            (512, 300, 16, False), (513, 300, 16, False), (1024, 257, 1, True),
+                                            (1025, 255, 2, True)])
+@pytest.mark.parametrize("sampled", [0, 1])
+def test_entry_operator_and_preconditioner_edges(n, m, rank, lp, sampled):
+    rng = np.random.default_rng(n + m)
+    p = workloads.robust_completion(n, m, min(m, 5), seed=n) if lp else workloads.matrix_completion(n, rank, m, seed=n)
+    X, S = workloads.random_pd_pair(n, seed=n, spread=0.5)
+    pts = [X, np.zeros(m), S]
+    if lp:
+        ell = len(p["lp"]["c"])
+        pts += [np.exp(rng.standard_normal(ell)), np.exp(rng.standard_normal(ell))]
+    with Context(p, rank_fixed=rank, sparse_sandwich=sampled) as ctx:
+        ctx.set_point(*(torch.from_numpy(a).cuda() for a in pts))
+        g = ctx.get_scaling()
+        lam, V, r = g["lam"], g["V"].cpu().numpy(), g["r"]
+        assert r == rank
+        sp = {"n": n, "r": r, "tau": 0.5 * lam[r], "lam": lam, "V": V, "Q": V[:, :r], "Qp": V[:, r:],
+              "lam_top": lam[:r], "lam_perp": lam[r:]}
+        sig, E, AQ = rf.sigma_diag(sp), rf.e_matrix(sp), rf.aq_matrix(p, sp)
+        N = ctx.aug_dim()
+        x = rng.standard_normal(N)
+        if lp:
+            lsp = rf.lp_split(sp, ctx.lp_split()["w"].cpu().numpy(), cap=int(ctx.options.lp_top_max))
+            ref = np.concatenate(rf.aug_apply_lp(p, sp, lsp, E, sig, x[:m], x[m:]))
+            AQ, sig = rf.aq_matrix_lp(p, sp, lsp), np.concatenate([sig, lsp["sig"]])
+        else:
+            ref = np.concatenate(rf.aug_apply(p, sp, E, sig, x[:m], x[m:]))
+        assert N == ref.size
+        for shift in (0, 1):  # vectors that are only 8-byte aligned too
+            buf = torch.zeros(N + shift, dtype=torch.float64, device="cuda")
+            buf[shift:] = torch.from_numpy(x)
+            got = ctx.newton_apply(buf[shift:]).cpu().numpy()
+            assert np.abs(got - ref).max() <= 1e-10 * np.abs(ref).max()
+            z = ctx.precond_apply(buf[shift:]).cpu().numpy()
+            # [beta I, AQ; AQ^T, -tau^2 Sigma] z = x
+            Pz = np.concatenate([g["beta"] * z[:m] + AQ @ z[m:], AQ.T @ z[:m] - sp["tau"] ** 2 * sig * z[m:]])
+            rows = np.concatenate([g["beta"] + np.abs(AQ).sum(1), np.abs(AQ).sum(0) + sp["tau"] ** 2 * sig])
+            assert np.abs(Pz - x).max() <= 1e-9 * rows.max() * np.abs(z).max()

@@ -175,8 +175,12 @@ void frob_norm(hipStream_t st, int n, const double* A, long lda, double* out, do
 // ---------------------------------------------------------------------------
 // In-place lower Cholesky; info (device int) receives 0 or the 1-based first bad pivot.
 void potrf(hipStream_t st, int n, double* A, long lda, int* info);
+// both of A and B (info[0], info[1]) by the same launches
+void potrf2(hipStream_t st, int n, double* A, double* B, long lda, int* info);
 // Linv = L^{-1}; `work` holds >= n * n doubles.
 void trtri(hipStream_t st, int n, const double* L, long ldl, double* Linv, long ldi, double* work);
+void trtri2(hipStream_t st, int n, const double* L, const double* M, long ld, double* Linv, double* Minv,
+            double* work);
 
 // ---------------------------------------------------------------------------
 // jacobi.hip

@@ -691,16 +691,14 @@ void ensure_scaling(sdp_ctx* c) {
     };
     // Cholesky factors X = L L^T, S = Rs Rs^T
     copy(st, nn, c->X, c->L);
-    potrf(st, n, c->L, n, c->info.get());
     copy(st, nn, c->S, c->Rs);
-    potrf(st, n, c->Rs, n, c->info.get() + 1);
+    potrf2(st, n, c->L, c->Rs, n, c->info.get());
     int hinfo[2] = {0, 0};
     WC_HIP(hipMemcpyAsync(hinfo, c->info.get(), 2 * sizeof(int), hipMemcpyDeviceToHost, st));
     WC_HIP(hipStreamSynchronize(st));
     if (hinfo[0]) throw Error(kENumeric, "X is not positive definite (pivot " + std::to_string(hinfo[0]) + ")");
     if (hinfo[1]) throw Error(kENumeric, "S is not positive definite (pivot " + std::to_string(hinfo[1]) + ")");
-    trtri(st, n, c->L, n, c->Linv, n, c->T1);
-    trtri(st, n, c->Rs, n, c->Rinv, n, c->T1);
+    trtri2(st, n, c->L, c->Rs, n, c->Linv, c->Rinv, c->T1);
     // NT factor: Rs^T L = U D V^T, G = L V D^{-1/2}, G^{-1} = D^{1/2} V^T L^{-1}
     // Both Jacobi runs are warm-started from the previous iterate's vectors V0
     // (Jacobi on A V0 with the rotations accumulated onto V0): consecutive

@@ -146,3 +146,29 @@ def test_entry_operator_and_preconditioner_edges(n, m, rank, lp, sampled):
             Pz = np.concatenate([g["beta"] * z[:m] + AQ @ z[m:], AQ.T @ z[:m] - sp["tau"] ** 2 * sig * z[m:]])
             rows = np.concatenate([g["beta"] + np.abs(AQ).sum(1), np.abs(AQ).sum(0) + sp["tau"] ** 2 * sig])
             assert np.abs(Pz - x).max() <= 1e-9 * rows.max() * np.abs(z).max()
+
+
+# panels: one row past a block, an outer panel's edges (256, 512 | 513), inverse
+# blocks of 1024; the input's strict upper triangle is not read.  The bounds
+# are those of the factorisation's other checks.
+@pytest.mark.parametrize("n", [2, 30, 34, 63, 65, 96, 257, 289, 511, 514, 543, 769, 1023, 1025, 1060])
+def test_cholesky_and_inverse_edges(n):
+    rng = np.random.default_rng(n)
+    M = rng.standard_normal((n, n))
+    A = M @ M.T + n * np.eye(n)
+    Ad = la.to_dev(np.where(np.triu(np.ones((n, n)), 1) > 0, np.nan, A))
+    st, info = la.dpotrf(Ad)
+    assert st == 0 and info == 0
+    Lg, Lr = la.from_dev(Ad), np.linalg.cholesky(A)
+    assert not np.triu(Lg, 1).any()
+    assert np.abs(Lg - Lr).max() <= 50 * n * EPS * np.abs(Lr).max()
+    Xg = la.from_dev(la.dtrtri(la.to_dev(np.where(np.triu(np.ones((n, n)), 1) > 0, np.nan, Lr))))
+    ref = np.linalg.inv(Lr)
+    assert not np.triu(Xg, 1).any()
+    assert np.abs(Xg - ref).max() <= 100 * n * EPS * np.abs(ref).max()
+    # a bad pivot in the first, a middle and the last column
+    for j in (0, n // 2, n - 1):
+        B = A.copy()
+        B[j, j] = -1.0
+        st, info = la.dpotrf(la.to_dev(B))
+        assert st == -5 and info == j + 1

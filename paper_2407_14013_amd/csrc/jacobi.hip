@@ -7,7 +7,7 @@
 //   2. H is diagonalised in LDS with two-sided cyclic Jacobi (H = R D R^T),
 //   3. the 32 columns of A (and of V) are rotated by R with FP64 MFMA.
 // For small n one workgroup per pair does all three with its columns held in
-// LDS; for large n the three steps are separate launches over row chunks.
+// LDS; for large n the steps are two or three launches over row chunks.
 // A sweep in which every pair was already orthogonal to within
 // tol * ||a_i|| ||a_j|| ends the iteration.  Rotating only the columns of A
 // gives the singular values with high relative accuracy, which the small
@@ -135,23 +135,28 @@ __device__ __forceinline__ double lane_xor(double v) {
     else return __shfl_xor(v, X, 64);
 }
 
-// The state of the cross rotations: lane (g, l) = (lane / 16, lane % 16) holds,
-// for a = l ^ 4g and the four b = 4g + q, the entries of H at the rows a and
-// 16 + (a ^ s) and the columns b and 16 + (b ^ s) of the current step's pairing
-// i <-> 16 + (i ^ s), and the entries of R at the rows l and 16 + l of those
-// columns; d1, d2, e are the pair a's own 2 x 2 block (replicated in the four
-// lanes that share a).
-struct CrossState {
-    double h11[4], h12[4], h21[4], h22[4], r11[4], r12[4], r21[4], r22[4], d1, d2, e;
+// The cross rotations of a round, by two waves.  Wave 0 holds H: lane (g, l) =
+// (lane / 16, lane % 16) holds, for a = l ^ 4g and the four b = 4g + q, the
+// entries at the rows a and 16 + (a ^ s) and the columns b and 16 + (b ^ s) of
+// the current step's pairing i <-> 16 + (i ^ s); d1, d2, e are the pair a's own
+// 2 x 2 block (replicated in the four lanes that share a).  It hands the 16
+// rotations of a step to wave 1 through LDS, which accumulates R (rows l and
+// 16 + l of the same columns) while wave 0 works on the next step.
+struct CrossH {
+    double h11[4], h12[4], h21[4], h22[4], d1, d2, e;
+};
+struct CrossR {
+    double r11[4], r12[4], r21[4], r22[4];
 };
 
-// One step: the 16 disjoint rotations (i, 16 + (i ^ s)), then, unless it was
-// the last, the move to the pairing s ^ D.  Only the entries whose row or
-// column partner changes move: by register renaming where D touches the two
-// low bits of b, by DPP where it touches a within a row of 16 lanes, through
-// the LDS crossbar for the three of the 16 steps with D = 4 or 8.
+// Wave 0's step: the 16 disjoint rotations (i, 16 + (i ^ s)), left in cs (c,
+// then s), then, unless it was the last, the move to the pairing s ^ D.  Only
+// the entries whose row or column partner changes move: by register renaming
+// where D touches the two low bits of b, by DPP where it touches a within a row
+// of 16 lanes, through the LDS crossbar for the three of the 16 steps with D =
+// 4 or 8.
 template <int D>
-__device__ __forceinline__ void cross_step(CrossState& z, int src) {
+__device__ __forceinline__ void cross_h(CrossH& z, int src, double* cs) {
     const int lane = threadIdx.x & 63;
     // the rotation of pair a (as jacobi_angle, without its early exit)
     const bool rot = z.e * z.e > 4.930380657631324e-32 * fabs(z.d1 * z.d2) && z.e != 0.0;
@@ -168,8 +173,13 @@ __device__ __forceinline__ void cross_step(CrossState& z, int src) {
     rc = rc * fma(-0.5 * u * rc, rc, 1.5);
     rc = rc * fma(-0.5 * u * rc, rc, 1.5);
     const double ca = rot ? rc : 1.0, sa = t * ca;
+    if (lane < 16) {  // a = lane there
+        cs[lane] = ca;
+        cs[16 + lane] = sa;
+    }
     z.d1 -= t * z.e;
     z.d2 += t * z.e;
+    if constexpr (D == 0) return;  // the last step: H is not needed any more
     // the rotation of pair b = 4g + q sits in lane q of the row (a = q ^ 4g = b)
     const double cb[4] = {dpp_mov<0x150>(ca), dpp_mov<0x151>(ca), dpp_mov<0x152>(ca), dpp_mov<0x153>(ca)};
     const double sb[4] = {dpp_mov<0x150>(sa), dpp_mov<0x151>(sa), dpp_mov<0x152>(sa), dpp_mov<0x153>(sa)};
@@ -182,43 +192,67 @@ __device__ __forceinline__ void cross_step(CrossState& z, int src) {
         z.h21[q] = sa * t11 + ca * t21;
         z.h22[q] = sa * t12 + ca * t22;
     }
+    double a12[4], a22[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
+        if constexpr (D < 4) {
+            a12[q] = z.h12[q ^ D];
+            a22[q] = lane_xor<D>(z.h22[q ^ D]);
+        } else {
+            a12[q] = lane_xor<5 * D>(z.h12[q]);
+            a22[q] = lane_xor<4 * D>(z.h22[q]);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        z.h12[q] = a12[q];
+        z.h21[q] = lane_xor<D>(z.h21[q]);
+        z.h22[q] = a22[q];
+    }
+    z.d2 = lane_xor<D>(z.d2);
+    // the pair a's new off-diagonal entry sits at b = a: row a / 4, lane and q = a % 4
+    const double e01 = (lane & 1) ? z.h12[1] : z.h12[0], e23 = (lane & 1) ? z.h12[3] : z.h12[2];
+    z.e = __shfl((lane & 2) ? e23 : e01, src, 64);
+}
+
+// Wave 1's step.
+template <int D>
+__device__ __forceinline__ void cross_r(CrossR& z, const double* cs) {
+    const int g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const double c = cs[4 * g + q], s = cs[16 + 4 * g + q];
         const double p1 = z.r11[q], p2 = z.r12[q], p3 = z.r21[q], p4 = z.r22[q];
-        z.r11[q] = cb[q] * p1 - sb[q] * p2;
-        z.r12[q] = sb[q] * p1 + cb[q] * p2;
-        z.r21[q] = cb[q] * p3 - sb[q] * p4;
-        z.r22[q] = sb[q] * p3 + cb[q] * p4;
+        z.r11[q] = c * p1 - s * p2;
+        z.r12[q] = s * p1 + c * p2;
+        z.r21[q] = c * p3 - s * p4;
+        z.r22[q] = s * p3 + c * p4;
     }
-    if constexpr (D != 0) {
-        double a12[4], a22[4], b12[4], b22[4];
+    if constexpr (D == 0) return;
+    double b12[4], b22[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if constexpr (D < 4) {
-                a12[q] = z.h12[q ^ D];
-                a22[q] = lane_xor<D>(z.h22[q ^ D]);
-                b12[q] = z.r12[q ^ D];
-                b22[q] = z.r22[q ^ D];
-            } else {
-                a12[q] = lane_xor<5 * D>(z.h12[q]);
-                a22[q] = lane_xor<4 * D>(z.h22[q]);
-                b12[q] = lane_xor<4 * D>(z.r12[q]);
-                b22[q] = lane_xor<4 * D>(z.r22[q]);
-            }
+    for (int q = 0; q < 4; ++q) {
+        if constexpr (D < 4) {
+            b12[q] = z.r12[q ^ D];
+            b22[q] = z.r22[q ^ D];
+        } else {
+            b12[q] = lane_xor<4 * D>(z.r12[q]);
+            b22[q] = lane_xor<4 * D>(z.r22[q]);
         }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            z.h12[q] = a12[q];
-            z.h21[q] = lane_xor<D>(z.h21[q]);
-            z.h22[q] = a22[q];
-            z.r12[q] = b12[q];
-            z.r22[q] = b22[q];
-        }
-        z.d2 = lane_xor<D>(z.d2);
-        // the pair a's new off-diagonal entry sits at b = a: row a / 4, lane and q = a % 4
-        const double e01 = (lane & 1) ? z.h12[1] : z.h12[0], e23 = (lane & 1) ? z.h12[3] : z.h12[2];
-        z.e = __shfl((lane & 2) ? e23 : e01, src, 64);
     }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        z.r12[q] = b12[q];
+        z.r22[q] = b22[q];
+    }
+}
+
+// Gray code: step t pairs with s = t ^ (t >> 1), so D is the lowest set bit of t + 1
+template <int T = 0, class F>
+__device__ __forceinline__ void cross_steps(F f) {
+    constexpr int D = T == 15 ? 0 : (T + 1) & -(T + 1);
+    f(std::integral_constant<int, D>{}, T);
+    if constexpr (T < 15) cross_steps<T + 1>(f);
 }
 
 // One pass of Jacobi rotations over the 256 pairs (i, 16 + j) of the 32 x 32
@@ -228,65 +262,67 @@ __device__ __forceinline__ void cross_step(CrossState& z, int src) {
 // (inner_jacobi does it in the sweep's first round), so a round's chain of
 // dependent steps is 16 instead of 31: simulated on NT factors and scaling
 // matrices (n = 48 .. 300), a decomposition takes 0 to 2 more sweeps of 8 to
-// 17.  Bound by the latency of that chain (the angle's ~25 dependent FP64
-// operations per step); one wave with everything in registers needs no barrier
-// and no LDS round trip in it.  At n = 1000 the pair kernel went from 19.9 to
-// 9.9 us per round and a scaling point from 74.9 to 53.8 ms.  Wave 0 of the
-// workgroup calls this; H is only read.
-__device__ __forceinline__ void cross_jacobi(const double (*H)[JW + 1], double (*R)[JW + 1]) {
-    const int lane = threadIdx.x & 63, l = lane & 15, g = lane >> 4, a = l ^ (4 * g);
-    const int src = 16 * (a >> 2) + (a & 3);
-    CrossState z;
+// 17.  Bound by the ~166 instructions one wave issues per step (the angle's and
+// the 64 of H's update), everything in registers: with R's 32 in the same wave a
+// pass took 6.1 us and a round at n = 200 19.5; with R in a second wave 18.5.  Every thread of
+// the workgroup calls this (one barrier per step); cs is a 16 x 32 work array.
+__device__ __forceinline__ void cross_jacobi(const double (*H)[JW + 1], double (*cs)[JW + 1], double (*R)[JW + 1]) {
+    const int lane = threadIdx.x & 63, l = lane & 15, g = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // a scalar: the waves part ways
+    if (wave == 0) {
+        const int a = l ^ (4 * g), src = 16 * (a >> 2) + (a & 3);
+        CrossH z;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int b = 4 * g + q;
-        z.h11[q] = H[a][b];
-        z.h12[q] = H[a][16 + b];
-        z.h21[q] = H[16 + a][b];
-        z.h22[q] = H[16 + a][16 + b];
-        z.r11[q] = l == b ? 1.0 : 0.0;
-        z.r12[q] = 0.0;
-        z.r21[q] = 0.0;
-        z.r22[q] = l == b ? 1.0 : 0.0;
-    }
-    z.d1 = H[a][a];
-    z.d2 = H[16 + a][16 + a];
-    z.e = H[a][16 + a];
-    // Gray code: step t pairs with s = t ^ (t >> 1), so D is the lowest set bit of t + 1
-    cross_step<1>(z, src);
-    cross_step<2>(z, src);
-    cross_step<1>(z, src);
-    cross_step<4>(z, src);
-    cross_step<1>(z, src);
-    cross_step<2>(z, src);
-    cross_step<1>(z, src);
-    cross_step<8>(z, src);
-    cross_step<1>(z, src);
-    cross_step<2>(z, src);
-    cross_step<1>(z, src);
-    cross_step<4>(z, src);
-    cross_step<1>(z, src);
-    cross_step<2>(z, src);
-    cross_step<1>(z, src);
-    cross_step<0>(z, src);
-    constexpr int s = 15 ^ (15 >> 1);  // the last step's pairing
+        for (int q = 0; q < 4; ++q) {
+            const int b = 4 * g + q;
+            z.h11[q] = H[a][b];
+            z.h12[q] = H[a][16 + b];
+            z.h21[q] = H[16 + a][b];
+            z.h22[q] = H[16 + a][16 + b];
+        }
+        z.d1 = H[a][a];
+        z.d2 = H[16 + a][16 + a];
+        z.e = H[a][16 + a];
+        cross_steps([&](auto d, int t) {
+            cross_h<decltype(d)::value>(z, src, cs[t]);
+            __syncthreads();
+        });
+    } else if (wave == 1) {
+        CrossR z;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int b = 4 * g + q;
-        R[l][b] = z.r11[q];
-        R[l][16 + (b ^ s)] = z.r12[q];
-        R[16 + l][b] = z.r21[q];
-        R[16 + l][16 + (b ^ s)] = z.r22[q];
+        for (int q = 0; q < 4; ++q) {
+            z.r11[q] = l == 4 * g + q ? 1.0 : 0.0;
+            z.r12[q] = 0.0;
+            z.r21[q] = 0.0;
+            z.r22[q] = z.r11[q];
+        }
+        cross_steps([&](auto d, int t) {
+            __syncthreads();
+            cross_r<decltype(d)::value>(z, cs[t]);
+        });
+        constexpr int s = 15 ^ (15 >> 1);  // the last step's pairing
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int b = 4 * g + q;
+            R[l][b] = z.r11[q];
+            R[l][16 + (b ^ s)] = z.r12[q];
+            R[16 + l][b] = z.r21[q];
+            R[16 + l][16 + (b ^ s)] = z.r22[q];
+        }
+    } else {
+#pragma unroll 1
+        for (int t = 0; t < 16; ++t) __syncthreads();
     }
 }
 
 // ---------------------------------------------------------------------------
-// Large-n round: three launches, so that a round keeps the whole chip busy
+// Large-n round: two or three launches, so that a round keeps the whole chip busy
 // instead of one workgroup per block pair walking all n rows.
 //   gram:   (pair, 128-row chunk) workgroups write partial 32 x 32 Gram matrices;
 //   pair:   one workgroup per pair sums them, tests the pair, diagonalises H
 //           and writes R (or marks the pair as already orthogonal);
-//   rotate: (pair, chunk, A or V) workgroups apply R to their rows.
+//   rotate: (pair, chunk, A or V) workgroups apply R to their rows;
+//   apply:  pair and rotate in one, up to a workgroup per CU.
 // ---------------------------------------------------------------------------
 constexpr int JCH = 128;  // rows per chunk
 
@@ -345,46 +381,37 @@ __global__ __launch_bounds__(256) void jacobi_gram_kernel(int n, int nblk, int r
         out[(hi * 16 + (lane >> 4) + 4 * v) * JW + hj * 16 + (lane & 15)] = acc[v] + acc2[v];
 }
 
-__global__ __launch_bounds__(256) void jacobi_pair_kernel(int nchunks, const double* __restrict__ part,
-                                                          double* __restrict__ Rout, int* __restrict__ skip,
-                                                          double tol, unsigned long long* offmax,
-                                                          const int* __restrict__ done, int inner_sweeps, int round) {
-    if (*done) return;
-    __shared__ double H[JW][JW + 1], Hs[JW][JW + 1], R[JW][JW + 1];
-    __shared__ double red[4];
-    __shared__ int rot_any;
-    const int w = blockIdx.x;
+// The partial Gram matrices of pair w summed in chunk order into H; returns the
+// pair's largest |H_ij| / sqrt(H_ii H_jj).  A thread's entries have PB chunks of
+// loads in flight (a plain loop waits for every load before the next).
+template <int NT>  // threads
+__device__ __forceinline__ double pair_gram(int nchunks, const double* __restrict__ src, double (*H)[JW + 1],
+                                            double* red) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const double* src = part + (long)w * nchunks * (JW * JW);
-    // the partial Gram matrices summed in chunk order; each thread owns four
-    // entries and keeps PB chunks of loads in flight (a plain loop waits for
-    // every load before the next)
-    {
-        constexpr int PB = 8, NQ = JW * JW / 256;
-        double sum[NQ];
+    constexpr int PB = 8, NQ = JW * JW / NT;
+    double sum[NQ];
 #pragma unroll
-        for (int q = 0; q < NQ; ++q) sum[q] = 0.0;
-        int ch = 0;
-        for (; ch + PB <= nchunks; ch += PB) {
-            double v[PB][NQ];
+    for (int q = 0; q < NQ; ++q) sum[q] = 0.0;
+    int ch = 0;
+    for (; ch + PB <= nchunks; ch += PB) {
+        double v[PB][NQ];
 #pragma unroll
-            for (int u = 0; u < PB; ++u)
+        for (int u = 0; u < PB; ++u)
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) v[u][q] = src[(long)(ch + u) * (JW * JW) + tid + 256 * q];
+            for (int q = 0; q < NQ; ++q) v[u][q] = src[(long)(ch + u) * (JW * JW) + tid + NT * q];
 #pragma unroll
-            for (int u = 0; u < PB; ++u)
+        for (int u = 0; u < PB; ++u)
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) sum[q] += v[u][q];
-        }
-        for (; ch < nchunks; ++ch)
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) sum[q] += src[(long)ch * (JW * JW) + tid + 256 * q];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) H[(tid + 256 * q) / JW][(tid + 256 * q) % JW] = sum[q];
+            for (int q = 0; q < NQ; ++q) sum[q] += v[u][q];
     }
+    for (; ch < nchunks; ++ch)
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) sum[q] += src[(long)ch * (JW * JW) + tid + NT * q];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) H[(tid + NT * q) / JW][(tid + NT * q) % JW] = sum[q];
     __syncthreads();
     double mx = 0.0;
-    for (int t = tid; t < JW * JW; t += 256) {
+    for (int t = tid; t < JW * JW; t += NT) {
         const int i = t % JW, j = t / JW;
         if (i < j) {
             const double hii = H[i][i], hjj = H[j][j];
@@ -395,21 +422,109 @@ __global__ __launch_bounds__(256) void jacobi_pair_kernel(int nchunks, const dou
     for (int off = 32; off > 0; off >>= 1) mx = fmax(mx, __shfl_xor(mx, off, 64));
     if (lane == 0) red[wave] = mx;
     __syncthreads();
-    const double off_pair = sqrt(fmax(fmax(red[0], red[1]), fmax(red[2], red[3])));
+    mx = red[0];
+#pragma unroll
+    for (int q = 1; q < NT / 64; ++q) mx = fmax(mx, red[q]);
+    return sqrt(mx);
+}
+
+// The rotations of a pair: R from H.  It need not be diagonalised exactly: the
+// outer sweeps revisit it, and convergence is judged by the tolerance test only.
+__device__ __forceinline__ void pair_rotations(double (*H)[JW + 1], double (*Hs)[JW + 1], double (*R)[JW + 1],
+                                               int* rot_any, int inner_sweeps, int round) {
+    if (round == 0 || inner_sweeps > 1) {
+        inner_jacobi(H, Hs, R, inner_sweeps, rot_any);
+    } else {
+        cross_jacobi(H, Hs, R);
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(256) void jacobi_pair_kernel(int nchunks, const double* __restrict__ part,
+                                                          double* __restrict__ Rout, int* __restrict__ skip,
+                                                          double tol, unsigned long long* offmax,
+                                                          const int* __restrict__ done, int inner_sweeps, int round) {
+    if (*done) return;
+    __shared__ double H[JW][JW + 1], Hs[JW][JW + 1], R[JW][JW + 1];
+    __shared__ double red[4];
+    __shared__ int rot_any;
+    const int w = blockIdx.x, tid = threadIdx.x;
+    const double off_pair = pair_gram<256>(nchunks, part + (long)w * nchunks * (JW * JW), H, red);
     if (tid == 0) {
         atomicMax(offmax, static_cast<unsigned long long>(__double_as_longlong(off_pair)));
         skip[w] = off_pair <= tol ? 1 : 0;
     }
     if (off_pair <= tol) return;  // uniform across the workgroup
-    // The pair need not be diagonalised exactly: the outer sweeps revisit it,
-    // and convergence is judged only by the tolerance test above.
-    if (round == 0 || inner_sweeps > 1) {
-        inner_jacobi(H, Hs, R, inner_sweeps, &rot_any);
-    } else {
-        if (wave == 0) cross_jacobi(H, R);
-        __syncthreads();
-    }
+    pair_rotations(H, Hs, R, &rot_any, inner_sweeps, round);
     for (int t = tid; t < JW * JW; t += 256) Rout[(long)w * (JW * JW) + t] = R[t / JW][t % JW];
+}
+
+// Pair and rotate in one launch, for rounds whose workgroups all have a CU of
+// their own: (pair, chunk, A or V) of 256 threads, or when those are too many
+// (pair, chunk) of 512, waves 0 .. 3 on A and 4 .. 7 on V.  Each works the
+// rotations of its pair out itself (bit for bit the same) with its rows already in
+// registers, as MFMA operands, so neither R, nor a launch, nor the rows' load is
+// waited for.  Bound by the chain of the 16 rotation steps.  A round (with its
+// Gram launch) went from 21.6 to 17.4 us at n = 300 and from 25.1 to 21.3 at n =
+// 1000; past a workgroup per CU the repeated work costs more (n = 1400: 33 us in
+// three launches, 36 so).
+template <int NT>
+__global__ __launch_bounds__(NT) void jacobi_apply_kernel(int n, int nblk, int round, int nchunks,
+                                                          const double* __restrict__ part, double* __restrict__ A,
+                                                          long lda, double* __restrict__ V, long ldv, double tol,
+                                                          unsigned long long* offmax, const int* __restrict__ done,
+                                                          int inner_sweeps) {
+    if (*done) return;
+    __shared__ double H[JW][JW + 1], Hs[JW][JW + 1], R[JW][JW + 1];
+    __shared__ double red[NT / 64];
+    __shared__ int rot_any;
+    const int w = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const bool mine = NT == 512 ? wave < 4 : blockIdx.z == 0;
+    double* M = mine ? A : V;
+    const long ldm = mine ? lda : ldv;
+    int bi, bj;
+    tournament_pair(round, w, nblk, bi, bj);
+    auto col = [&](int c) { return c < JB ? bi * JB + c : bj * JB + (c - JB); };  // >= n in the padding
+    // the wave's 32 rows, two tiles of 16; loads at clamped places
+    const int row0 = blockIdx.y * JCH + (wave & 3) * 32 + (lane & 15);
+    double mv[2][JW / 4];
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt)
+#pragma unroll
+        for (int k = 0; k < JW / 4; ++k)
+            mv[rt][k] = M[min(row0 + 16 * rt, n - 1) + (long)min(col(4 * k + (lane >> 4)), n - 1) * ldm];
+    const double off_pair = pair_gram<NT>(nchunks, part + (long)w * nchunks * (JW * JW), H, red);
+    if (tid == 0 && blockIdx.y == 0 && blockIdx.z == 0)
+        atomicMax(offmax, static_cast<unsigned long long>(__double_as_longlong(off_pair)));
+    if (off_pair <= tol) return;  // uniform across the workgroup
+    pair_rotations(H, Hs, R, &rot_any, inner_sweeps, round);
+    double rv[2][JW / 4];
+#pragma unroll
+    for (int jt = 0; jt < 2; ++jt)
+#pragma unroll
+        for (int k = 0; k < JW / 4; ++k) rv[jt][k] = R[4 * k + (lane >> 4)][jt * 16 + (lane & 15)];
+    // the transposed product, so that a store covers 16 consecutive rows of a column
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+        d4 o[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};
+#pragma unroll
+        for (int k = 0; k < JW / 4; ++k) {
+            // a padded column is zero, whatever the clamped load brought
+            const double m = col(4 * k + (lane >> 4)) < n ? mv[rt][k] : 0.0;
+#pragma unroll
+            for (int jt = 0; jt < 2; ++jt) o[jt] = __builtin_amdgcn_mfma_f64_16x16x4f64(rv[jt][k], m, o[jt], 0, 0, 0);
+        }
+        const int row = row0 + 16 * rt;
+        if (row < n) {
+#pragma unroll
+            for (int jt = 0; jt < 2; ++jt)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int gc = col(jt * 16 + (lane >> 4) + 4 * v);
+                    if (gc < n) M[row + (long)gc * ldm] = o[jt][v];
+                }
+        }
+    }
 }
 
 __global__ __launch_bounds__(256) void jacobi_rotate_kernel(int n, int nblk, int round, double* __restrict__ A,
@@ -578,7 +693,7 @@ __global__ __launch_bounds__(JT) void jacobi_round_lds_kernel(int n, int nblk, i
     if (round == 0 || inner_sweeps > 1) {
         inner_jacobi(H0, H1, R, inner_sweeps, &rot_any);
     } else {
-        if (wave == 0) cross_jacobi(H0, R);
+        cross_jacobi(H0, H1, R);
         __syncthreads();
     }
 
@@ -755,13 +870,25 @@ JacobiWork::~JacobiWork() {
     if (pinned) (void)hipHostFree(pinned);
 }
 
-// One round of the large-n form (three launches; see the kernels above).
+// One round of the large-n form (see the kernels above).
+constexpr long CUS = 256;
 static void split_round(hipStream_t st, int n, int nblk, int round, double* A, long lda, double* V, long ldv,
                         double tol, unsigned long long* off, const int* flags, JacobiWork& w) {
     const int npairs = nblk / 2, nchunks = cdiv(n, JCH);
     hipLaunchKernelGGL(jacobi_gram_kernel, dim3(npairs, nchunks), dim3(256), 0, st, n, nblk, round, A, lda,
                        w.part.get(), flags);
     WC_LAUNCH_CHECK();
+    const long wgs = (long)npairs * nchunks;
+    if (wgs * (V ? 2 : 1) <= CUS) {
+        hipLaunchKernelGGL(jacobi_apply_kernel<256>, dim3(npairs, nchunks, V ? 2 : 1), dim3(256), 0, st, n, nblk,
+                           round, nchunks, w.part.get(), A, lda, V, ldv, tol, off, flags, jacobi_inner_sweeps());
+        return;
+    }
+    if (wgs <= CUS && V) {
+        hipLaunchKernelGGL(jacobi_apply_kernel<512>, dim3(npairs, nchunks), dim3(512), 0, st, n, nblk, round, nchunks,
+                           w.part.get(), A, lda, V, ldv, tol, off, flags, jacobi_inner_sweeps());
+        return;
+    }
     hipLaunchKernelGGL(jacobi_pair_kernel, dim3(npairs), dim3(256), 0, st, nchunks, w.part.get(), w.rot.get(),
                        w.skip.get(), tol, off, flags, jacobi_inner_sweeps(), round);
     WC_LAUNCH_CHECK();

@@ -39,6 +39,26 @@ def test_jacobi_clustered_and_zero_columns(n):
     assert np.abs(A @ Vg - Aout).max() <= 20 * n * EPS * ref[0]
 
 
+# a round of two launches with A's and V's rows apart (n = 639: 20 pairs x 5 row
+# chunks), together (705, 1024: 32 x 8 workgroups), and of three launches (1025),
+# rows one past a chunk; with V and without
+@pytest.mark.parametrize("n", [639, 705, 769, 1024, 1025])
+def test_jacobi_large_round_forms(n):
+    rng = np.random.default_rng(n)
+    d = np.linspace(1.0, 3.0, n)
+    A = np.linalg.qr(rng.standard_normal((n, n)))[0] * d + 1e-3 * rng.standard_normal((n, n))
+    Ad = la.to_dev(A)
+    s, V, sweeps = la.djacobi_svd(Ad)
+    s, Vg, Aout = s.cpu().numpy(), la.from_dev(V), la.from_dev(Ad)
+    ref = np.linalg.svd(A, compute_uv=False)
+    assert 1 <= sweeps <= 60
+    assert np.abs(s - ref).max() <= 20 * n * EPS * ref[0]
+    assert np.abs(Vg.T @ Vg - np.eye(n)).max() <= 20 * n * EPS
+    assert np.abs(A @ Vg - Aout).max() <= 20 * n * EPS * ref[0]
+    s1, _, _ = la.djacobi_svd(la.to_dev(A), want_v=False)
+    assert np.abs(s1.cpu().numpy() - ref).max() <= 20 * n * EPS * ref[0]
+
+
 # script-A script-Q rows of 63..65, 126..129 and 255..257 entries (the register
 # forms of the batched Krylov loop and the general one), n at the default
 # tile's edge, odd numbers of packed pairs, and (rank_max 79) vectors that do

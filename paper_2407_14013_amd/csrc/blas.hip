@@ -23,6 +23,21 @@ typedef double d2 __attribute__((ext_vector_type(2)));
 constexpr int GBIG = 128;  // tile edge for large products
 constexpr size_t dgemm_lds(int bm, int bn) { return sizeof(double) * 2 * GBK * (bm + 1 + bn + 1); }
 
+// The workgroup's output tile (modes as below).
+__device__ __forceinline__ void gemm_tile(int tri, int& bx, int& by) {
+    bx = blockIdx.x;
+    by = blockIdx.y;
+    if (tri != 3) return;
+    const int P = gridDim.x, id = blockIdx.x, x8 = id & 7;
+    const int base = P >> 3, rem = P & 7;
+    const int t = x8 * base + min(x8, rem) + (id >> 3);
+    int x = static_cast<int>((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
+    while (x * (x + 1) / 2 > t) --x;
+    while ((x + 1) * (x + 2) / 2 <= t) ++x;
+    bx = x;
+    by = t - x * (x + 1) / 2;
+}
+
 // Block tile BM x BN (64 x 64 or 128 x 128), four waves in a 2 x 2 grid, each
 // wave (BM/2) x (BN/2) of 16 x 16 FP64 MFMA tiles.  K advances GBK at a time
 // through double-buffered LDS (dynamic, 2 GBK (BM + BN + 2) doubles) with
@@ -51,17 +66,8 @@ __global__ __launch_bounds__(256) void dgemm_kernel(int M, int N, int K, double 
                                                     long sB, long sC, int klast) {
     // split-K launches give the last z-slice the remainder of K
     if (klast > 0 && blockIdx.z == gridDim.z - 1) K = klast;
-    int bx = blockIdx.x, by = blockIdx.y;
-    if (tri == 3) {
-        const int P = gridDim.x, id = blockIdx.x, x8 = id & 7;
-        const int base = P >> 3, rem = P & 7;
-        const int t = x8 * base + min(x8, rem) + (id >> 3);
-        int x = static_cast<int>((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
-        while (x * (x + 1) / 2 > t) --x;
-        while ((x + 1) * (x + 2) / 2 <= t) ++x;
-        bx = x;
-        by = t - x * (x + 1) / 2;
-    }
+    int bx, by;
+    gemm_tile(tri, bx, by);
     const int tile_m = bx * BM;
     const int tile_n = by * BN;
     if (tri == 1 && tile_n > tile_m + BM - 1) return;
@@ -210,6 +216,182 @@ __global__ __launch_bounds__(256) void dgemm_kernel(int M, int N, int K, double 
             }
 }
 
+// The 128 x 128 form for operands that 16-byte loads can reach (dma_ok): the
+// same tiles and sums, bit for bit, but an operand goes from global memory into
+// LDS without passing through registers (global_load_lds, 1 KB per
+// instruction), and no load has a bounds check.  FP64 MFMA (64 cycles per
+// instruction) shares the SIMD's issue with everything else, so the time goes
+// with the other instructions of a step: 64 MFMA to 16 loads, 16 LDS stores and
+// 60 address operations and register moves in the form above, to 8 loads here.
+// n = 4096: 2.23 ms (61.7 TF) before, 2.10 now (65.3); n = 4000, where edge tiles
+// took the checked loads: 2.21 ms, 1.94 now.
+//
+// Operand contiguous along its tile index (A, or B^T): LDS row k holds the 128
+// entries, one instruction per row; pitch 144, so that the two rows a half-wave
+// reads lie in different halves of the banks.  Contiguous along k: an
+// instruction brings 8 columns of 16 k-values as 64 pieces of 16 bytes, column i's
+// piece p at slot 8 (i % 8) + (p ^ ((i / 2) % 8)), which spreads the 16 columns
+// of a fragment read over all banks.  Past the edges of the matrix a load takes
+// a place inside it (the outputs are not stored; factors past K count as zero).
+constexpr int DMA_P = GBIG + 16;           // pitch of a k-row
+constexpr int DMA_T = GBK * DMA_P;         // doubles of an operand's stage
+constexpr size_t DMA_LDS = sizeof(double) * 4 * DMA_T;
+
+// A uniform pointer, known to be one (scalar base, 32-bit lane offset in the load)
+__device__ __forceinline__ const char* scalar_ptr(const double* p) {
+    const uintptr_t v = reinterpret_cast<uintptr_t>(p);
+    const unsigned lo = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v));
+    const unsigned hi = __builtin_amdgcn_readfirstlane(static_cast<unsigned>(v >> 32));
+    return reinterpret_cast<const char*>((static_cast<uintptr_t>(hi) << 32) | lo);
+}
+
+// 16 bytes per lane from p + off into LDS at dst (uniform), lane after lane
+__device__ __forceinline__ void dma16(const double* p, unsigned off, double* dst) {
+    __builtin_amdgcn_global_load_lds(scalar_ptr(p) + off, dst, 16, 0, 0);
+}
+
+template <bool KC>  // contiguous along k
+struct DmaOperand {
+    const double* src[4];      // uniform: where this wave's four instructions read at the next step
+    long ld;
+    unsigned off[KC ? 4 : 1];  // per lane, bytes
+    int frag;                  // LDS offset of the first fragment
+
+    // dim: extent of the tile index; t0: the tile's start; w0: the wave's first entry
+    __device__ __forceinline__ void init(const double* X, long ldx, int t0, int dim, int w0) {
+        const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        ld = ldx;
+        if constexpr (KC) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = 8 * (4 * q + wave) + (lane >> 3);
+                src[q] = X + (long)t0 * ldx;
+                off[q] = static_cast<unsigned>((long)min(i, dim - 1 - t0) * ldx + 2 * ((lane & 7) ^ ((i >> 1) & 7))) * 8u;
+            }
+            const int i = w0 + (lane & 15), b = (lane >> 5) ^ ((i >> 1) & 7);
+            frag = (i >> 3) * 128 + ((i & 7) * 8 + b) * 2 + ((lane >> 4) & 1);
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) src[q] = X + (4 * q + wave) * ldx;
+            off[0] = static_cast<unsigned>(min(t0 + 2 * lane, dim - 2)) * 8u;
+            frag = (lane >> 4) * DMA_P + w0 + (lane & 15);
+        }
+    }
+    // the next step's loads; left: k-values from that step on
+    __device__ __forceinline__ void issue(bool tail, int left, double* stage) {
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int g = 4 * q + wave;
+            if constexpr (KC) {
+                unsigned o = off[q];
+                if (tail) {  // pieces past K: the last one
+                    const int i = 8 * g + ((threadIdx.x & 63) >> 3), pc = (threadIdx.x & 7) ^ ((i >> 1) & 7);
+                    o -= 8u * static_cast<unsigned>(max(2 * pc - (left - 2), 0));
+                }
+                dma16(src[q], o, stage + g * 128);
+                src[q] += GBK;
+            } else {
+                dma16(src[q] - (tail ? (long)max(g - (left - 1), 0) * ld : 0), off[0], stage + g * DMA_P);
+                src[q] += GBK * ld;
+            }
+        }
+    }
+    // fragment t (16 entries further on) of k4 = 4 q
+    __device__ __forceinline__ double get(const double* stage, int q, int t) const {
+        if constexpr (KC) return stage[(frag ^ (4 * q)) + t * 256];  // piece b ^ 2 q
+        else return stage[frag + q * 4 * DMA_P + t * 16];
+    }
+};
+
+template <bool TA, bool TB>
+__global__ __launch_bounds__(256, 2) void dgemm_dma_kernel(int M, int N, int K, const double* __restrict__ A, long lda,
+                                                        const double* __restrict__ B, long ldb, double* __restrict__ C,
+                                                        long ldc, int tri, long sA, long sB, long sC) {
+    int bx, by;
+    gemm_tile(tri, bx, by);
+    const int tile_m = bx * GBIG, tile_n = by * GBIG;
+    if (tri == 1 && tile_n > tile_m + GBIG - 1) return;
+    A += blockIdx.z * sA;
+    B += blockIdx.z * sB;
+    C += blockIdx.z * sC;
+    if (tri == 2) {
+        if (tile_m > tile_n + GBIG - 1) return;
+        const int ks = max(tile_m, tile_n);
+        A += TA ? (long)ks : (long)ks * lda;
+        B += TB ? (long)ks * ldb : (long)ks;
+        K -= ks;
+    }
+    extern __shared__ double gsm[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+    DmaOperand<TA> oa;
+    DmaOperand<!TB> ob;
+    oa.init(A, lda, tile_m, M, wm * 64);
+    ob.init(B, ldb, tile_n, N, wn * 64);
+    d4 acc[4][4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+    // stages: A0 A1 B0 B1
+    double* sA0 = gsm;
+    double* sB0 = gsm + 2 * DMA_T;
+    const int full = K / GBK, left = K % GBK;
+    auto issue = [&](int st) {
+        if (st < full) {
+            oa.issue(false, 0, sA0 + (st & 1) * DMA_T);
+            ob.issue(false, 0, sB0 + (st & 1) * DMA_T);
+        } else if (left > 0) {
+            oa.issue(true, left, sA0 + (st & 1) * DMA_T);
+            ob.issue(true, left, sB0 + (st & 1) * DMA_T);
+        }
+    };
+    auto step = [&](const double* sa, const double* sb, int q, bool in) {
+        double av[4], bv[4];
+#pragma unroll
+        for (int a = 0; a < 4; ++a) av[a] = oa.get(sa, q, a);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) bv[b] = ob.get(sb, q, b);
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int b = 0; b < 4; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(in ? av[a] : 0.0, in ? bv[b] : 0.0, acc[a][b], 0, 0, 0);
+    };
+    // a step's loads have landed, and everyone has read the other stage
+    auto turn = [] {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+    };
+    issue(0);
+#pragma unroll 1
+    for (int st = 0; st < full; ++st) {
+        turn();
+        issue(st + 1);
+        const double* sa = sA0 + (st & 1) * DMA_T;
+        const double* sb = sB0 + (st & 1) * DMA_T;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) step(sa, sb, q, true);
+    }
+    if (left > 0) {
+        turn();
+#pragma unroll 1
+        for (int q = 0; 4 * q < left; ++q)
+            step(sA0 + (full & 1) * DMA_T, sB0 + (full & 1) * DMA_T, q, 4 * q + (lane >> 4) < left);
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int gi = tile_m + wm * 64 + a * 16 + (lane >> 4) + 4 * v;
+                const int gj = tile_n + wn * 64 + b * 16 + (lane & 15);
+                if (gi < M && gj < N && ((tri != 1 && tri != 3) || gi >= gj)) C[gi + (long)gj * ldc] = acc[a][b][v];
+            }
+}
+
 // C = alpha sum_s P_s + beta C over the split-K partial products P_s (m x n, ld m).
 __global__ void dgemm_reduce_kernel(int M, int N, int splits, const double* __restrict__ P, double alpha, double beta,
                                     double* __restrict__ C, long ldc) {
@@ -233,11 +415,24 @@ __global__ void dgemm_reduce_kernel(int M, int N, int splits, const double* __re
 
 long dgemm_splitk_ws() { return (long)GEMM_SPLITS * GEMM_SPLIT_TILES * GBM * GBN; }
 
+// Whether every 16-byte load of dgemm_dma_kernel is aligned and inside its
+// operand: even leading dimensions, strides and contiguous extents, 16-byte
+// bases, tiles within 32-bit byte offsets.
+static bool dma_ok(bool ta, bool tb, int m, int n, int k, const double* A, long lda, const double* B, long ldb, long sA,
+                   long sB) {
+    return reinterpret_cast<uintptr_t>(A) % 16 == 0 && reinterpret_cast<uintptr_t>(B) % 16 == 0 && lda % 2 == 0 &&
+           ldb % 2 == 0 && sA % 2 == 0 && sB % 2 == 0 && (ta || m % 2 == 0) && (!tb || n % 2 == 0) &&
+           ((!ta && tb) || k % 2 == 0) && std::max(lda, ldb) <= (1L << 21);
+}
+
 template <bool TA, bool TB>
 static void dgemm_launch(hipStream_t st, dim3 grid, bool big, int m, int n, int k, double alpha, const double* A,
                          long lda, const double* B, long ldb, double beta, double* C, long ldc, int lo, long sA,
                          long sB, long sC, int klast) {
-    if (big)  // only with alpha == 1 and beta == 0
+    if (big && dma_ok(TA, TB, m, n, k, A, lda, B, ldb, sA, sB))  // big: only with alpha == 1 and beta == 0
+        hipLaunchKernelGGL((dgemm_dma_kernel<TA, TB>), grid, dim3(256), DMA_LDS, st, m, n, k, A, lda, B, ldb, C, ldc,
+                           lo, sA, sB, sC);
+    else if (big)
         hipLaunchKernelGGL((dgemm_kernel<TA, TB, GBIG, GBIG, 0>), grid, dim3(256), dgemm_lds(GBIG, GBIG), st, m, n, k,
                            1.0, A, lda, B, ldb, 0.0, C, ldc, lo, sA, sB, sC, klast);
     else if (beta == 0.0)
@@ -306,8 +501,15 @@ void dgemm(hipStream_t st, bool ta, bool tb, int m, int n, int k, double alpha, 
             return;
         }
     }
-    // 128 x 128 tiles once they still give every CU several workgroups (plain C = A B only)
-    const bool big = alpha == 1.0 && beta == 0.0 && (long)cdiv(m, GBIG) * cdiv(n, GBIG) * batch >= 4L * 256;
+    // 128 x 128 tiles (plain C = A B only).  Through registers they pay once every
+    // CU has several workgroups to hide the loads of one behind another; by
+    // LDS loads from well under one per CU, where they don't pad the product
+    // much more than 64 x 64 tiles do (n = 1500, 144 tiles: 226 us against 234;
+    // n = 1800, 225 tiles: 269 against 371; n = 3968, 961 tiles: 1.93 ms against 2.59).
+    const long t128 = (long)cdiv(m, GBIG) * cdiv(n, GBIG) * batch, t64 = (long)cdiv(m, GBM) * cdiv(n, GBN) * batch;
+    const bool big = alpha == 1.0 && beta == 0.0 &&
+                     (t128 >= 4L * 256 ||
+                      (t128 >= 160 && 40 * t128 <= 12 * t64 && dma_ok(ta, tb, m, n, k, A, lda, B, ldb, sA, sB)));
     if (big) launch(dim3(cdiv(m, GBIG), cdiv(n, GBIG), batch), true, k, alpha, beta, C, ldc, sA, sB, sC, 0);
     else launch(dim3(cdiv(m, GBM), cdiv(n, GBN), batch), false, k, alpha, beta, C, ldc, sA, sB, sC, 0);
 }

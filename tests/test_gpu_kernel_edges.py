@@ -192,3 +192,31 @@ def test_cholesky_and_inverse_edges(n):
         B[j, j] = -1.0
         st, info = la.dpotrf(la.to_dev(B))
         assert st == -5 and info == j + 1
+
+
+# 128 x 128 tiles by 16-byte LDS loads: K of 2 to one past a step, tiles with one
+# pair of rows or columns, 160 tiles and fewer (the general form); the same
+# operands 8 bytes further on take the general form and give the same bits.
+# The bound is that of the product's other checks.
+@pytest.mark.parametrize("ta", ["N", "T"])
+@pytest.mark.parametrize("tb", ["N", "T"])
+@pytest.mark.parametrize("m, n, k", [(4096, 4098, 2), (4098, 4096, 14), (4096, 4100, 16), (4226, 3970, 18),
+                                     (4100, 4100, 46), (4098, 4098, 130), (1666, 1602, 50), (2048, 1280, 34),
+                                     (1536, 1536, 34), (2049, 1801, 33)])
+def test_gemm_lds_loads_match_the_general_form(ta, tb, m, n, k):
+    rng = np.random.default_rng(m + n + k)
+    A = rng.standard_normal((k, m) if ta == "T" else (m, k))
+    B = rng.standard_normal((n, k) if tb == "T" else (k, n))
+    ref = (A.T if ta == "T" else A) @ (B.T if tb == "T" else B)
+
+    def shifted(a):
+        d = la.to_dev(a)
+        buf = torch.full((d.numel() + 1,), np.nan, dtype=torch.float64, device="cuda")
+        buf[1:] = d.flatten()
+        return buf[1:].view(d.shape)
+
+    got = [torch.full((n, m), np.nan, dtype=torch.float64, device="cuda") for _ in range(2)]
+    la.dgemm(ta, tb, 1.0, la.to_dev(A), la.to_dev(B), 0.0, got[0])
+    la.dgemm(ta, tb, 1.0, shifted(A), shifted(B), 0.0, got[1])
+    assert np.abs(la.from_dev(got[0]) - ref).max() <= 4 * k * EPS * np.abs(A).max() * np.abs(B).max()
+    assert torch.equal(got[0], got[1])

@@ -679,11 +679,12 @@ void sliced_values(hipStream_t st, long slots, const int* eidx, const double* u,
 }
 
 // Z[:, k0 + c] = Y E[:, k0 + c] for c < kc: the workgroup stages its KC
-// columns of E in LDS (Es[c n + q]: a slot's KC reads fall on banks spread
-// by its row q), then each wave walks slices and gathers E[q, k0 .. k0 + KC)
-// for every slot (p, q).  The slot stream (16-bit column, FP64 value) is
-// re-read once per workgroup from L2, which bounds the kernel; 16 waves per
-// workgroup keep enough of those loads in flight.  Sums run in slot order.
+// columns of E in LDS, then each wave walks slices and gathers E[q, k0 .. k0 +
+// KC) for every slot (p, q).  Bound by the bank conflicts of those gathers (64
+// unrelated rows q): two columns per 16-byte read take 355 us at n = 4000, m =
+// 160 000, one per read 384.  The slot stream (16-bit column, FP64 value) is
+// re-read once per workgroup from L2; 16 waves per workgroup keep enough of
+// those loads in flight.  Sums run in slot order.
 constexpr int YE_THREADS = 1024;
 template <int KC>
 __global__ __launch_bounds__(YE_THREADS) void sampled_ye_kernel(int n, int nsl, const int* __restrict__ sptr,
@@ -692,13 +693,18 @@ __global__ __launch_bounds__(YE_THREADS) void sampled_ye_kernel(int n, int nsl, 
                                                                 const double* __restrict__ val,
                                                                 const double* __restrict__ E, long lde,
                                                                 double* __restrict__ Z, long ldz) {
-    extern __shared__ double Es[];  // KC x n
+    extern __shared__ __attribute__((aligned(16))) double Es[];  // KC x n
     const int k0 = blockIdx.x * KC;
     const int kc = min(KC, n - k0);
+    // column c's entry q: columns in pairs, so that one 16-byte read brings two
+    auto at = [n](int c, int q) { return KC == 1 ? q : (c / 2) * 2 * n + 2 * q + (c & 1); };
+    for (int q = threadIdx.x; q < n; q += YE_THREADS) {
+        double v[KC];
 #pragma unroll
-    for (int c = 0; c < KC; ++c)
-        for (int q = threadIdx.x; q < n; q += YE_THREADS)
-            Es[c * n + q] = (c < kc) ? E[q + (long)(k0 + c) * lde] : 0.0;
+        for (int c = 0; c < KC; ++c) v[c] = E[q + (long)(k0 + min(c, kc - 1)) * lde];
+#pragma unroll
+        for (int c = 0; c < KC; ++c) Es[at(c, q)] = v[c];
+    }
     __syncthreads();
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     for (int s = wave; s < nsl; s += YE_THREADS / 64) {
@@ -719,13 +725,13 @@ __global__ __launch_bounds__(YE_THREADS) void sampled_ye_kernel(int n, int nsl, 
 #pragma unroll
             for (int h = 0; h < 4; ++h)
 #pragma unroll
-                for (int c = 0; c < KC; ++c) acc[c] += w[h] * Es[c * n + q[h]];
+                for (int c = 0; c < KC; ++c) acc[c] += w[h] * Es[at(c, q[h])];
         }
         for (; t < len; ++t) {
             const int q = ecol[e0 + 64 * t];
             const double w = val[e0 + 64 * t];
 #pragma unroll
-            for (int c = 0; c < KC; ++c) acc[c] += w * Es[c * n + q];
+            for (int c = 0; c < KC; ++c) acc[c] += w * Es[at(c, q)];
         }
         const int p = srow[s * 64 + lane];
         if (p >= 0) {
@@ -764,51 +770,106 @@ void sampled_ye(hipStream_t st, int n, int nsl, const int* sptr, const int* srow
     WC_LAUNCH_CHECK();
 }
 
-// out_i = E[:, j] . Z[:, k] for every constraint i = (j, k), j <= k, grouped
-// by j (dptr, dpart = k, didx = i): the workgroup of row j stages E[:, j] in
-// LDS and each wave takes one constraint at a time, reading Z[:, k]
-// coalesced with eight loads in flight per lane, then reducing across the
-// wave (fixed order).
-constexpr int DOT_U = 8;
-__global__ __launch_bounds__(256) void sampled_dots_kernel(int n, const int* __restrict__ dptr,
-                                                           const int* __restrict__ dpart,
-                                                           const int* __restrict__ didx,
-                                                           const double* __restrict__ E, long lde,
-                                                           const double* __restrict__ Z, long ldz,
-                                                           double* __restrict__ out) {
-    extern __shared__ double ej[];  // n
-    const int j = blockIdx.x;
-    const int g0 = dptr[j], g1 = dptr[j + 1];
-    if (g0 == g1) return;  // the whole workgroup leaves together
-    for (int q = threadIdx.x; q < n; q += 256) ej[q] = E[q + (long)j * lde];
-    __syncthreads();
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int g = g0 + wave; g < g1; g += 4) {
-        const double* zk = Z + (long)dpart[g] * ldz;
-        double s[DOT_U];
+// out_i = E[:, j] . Z[:, k] for every constraint i = (j, k), j <= k.  dpart lists
+// the k grouped by j, each j's padded to a multiple of four (repeats, didx =
+// -1), so that four entries share the j in dj; didx is the constraint.
+//
+// Z is far larger than an XCD's L2, and reading whole columns pair by pair ran
+// at the memory's rate (n = 4000, m = 160 000: 5.1 GB, 603 us).  Here the sums are
+// cut into slabs of SD_W rows, whose part of Z is 2 MB at n = 4000, and every XCD
+// (workgroups go to them in turn) takes each eighth slab for all pairs: its
+// workgroups, all resident, walk the slabs in step, and Z's part is read from L2.
+// Sixteen lanes take a pair, four pairs at a time with one read of E[:, j];
+// the XCDs' sums are added in a fixed order by the second kernel: 282 us.
+constexpr int SD_W = 64, SD_X = 8;
+constexpr int SD_B = 512;    // batches of four pairs that a workgroup holds at a time
+constexpr int SD_WGS = 64;   // workgroups per XCD: two per CU (four: 303 us)
+typedef double sd_d2 __attribute__((ext_vector_type(2), aligned(8)));
+
+template <bool WHOLE>
+__device__ __forceinline__ sd_d2 sd_load(const double* p, int left) {
+    if constexpr (WHOLE) return *reinterpret_cast<const sd_d2*>(p);
+    sd_d2 v = {0.0, 0.0};
+    if (left > 0) v.x = p[0];
+    if (left > 1) v.y = p[1];
+    return v;
+}
+
+// batches [i0, i1) of a slab; l: the lane's place among its sixteen, left: rows
+// from the lane's first one on
+template <bool WHOLE>
+__device__ __forceinline__ void sd_slab(int i0, int i1, int l, int left, const int* __restrict__ ks,
+                                        const int* __restrict__ js, const double* __restrict__ Eb, long lde,
+                                        const double* __restrict__ Zb, long ldz, double* __restrict__ acc) {
+    for (int i = i0; i < i1; ++i) {
+        const double* e = Eb + (long)js[i] * lde;
+        const double* z[4];
 #pragma unroll
-        for (int h = 0; h < DOT_U; ++h) s[h] = 0.0;
-        int q = lane;
-        for (; q + 64 * (DOT_U - 1) < n; q += 64 * DOT_U) {
-            double z[DOT_U];
+        for (int u = 0; u < 4; ++u) z[u] = Zb + (long)ks[4 * i + u] * ldz;
+        const sd_d2 e0 = sd_load<WHOLE>(e, left), e1 = sd_load<WHOLE>(e + SD_W / 2, left - SD_W / 2);
+        sd_d2 z0[4], z1[4];
 #pragma unroll
-            for (int h = 0; h < DOT_U; ++h) z[h] = zk[q + 64 * h];
-#pragma unroll
-            for (int h = 0; h < DOT_U; ++h) s[h] += ej[q + 64 * h] * z[h];
+        for (int u = 0; u < 4; ++u) {
+            z0[u] = sd_load<WHOLE>(z[u], left);
+            z1[u] = sd_load<WHOLE>(z[u] + SD_W / 2, left - SD_W / 2);
         }
         double v = 0.0;
-        for (; q < n; q += 64) v += ej[q] * zk[q];  // at most DOT_U - 1 more
 #pragma unroll
-        for (int h = 0; h < DOT_U; ++h) v += s[h];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        if (lane == 0) out[didx[g]] = v;
+        for (int u = 0; u < 4; ++u) {
+            const double s = row16_sum((e0.x * z0[u].x + e0.y * z0[u].y) + (e1.x * z1[u].x + e1.y * z1[u].y));
+            v = l == u ? s : v;
+        }
+        if (l < 4) acc[4 * i + l] += v;
     }
 }
-void sampled_dots(hipStream_t st, int n, const int* dptr, const int* dpart, const int* didx, const double* E, long lde,
-                  const double* Z, long ldz, double* out) {
-    hipLaunchKernelGGL(sampled_dots_kernel, dim3(n), dim3(256), sizeof(double) * n, st, n, dptr, dpart, didx, E, lde,
-                       Z, ldz, out);
+
+__global__ __launch_bounds__(256) void sampled_dots_kernel(int n, int nb, const int* __restrict__ dj,
+                                                           const int* __restrict__ dpart,
+                                                           const double* __restrict__ E, long lde,
+                                                           const double* __restrict__ Z, long ldz,
+                                                           double* __restrict__ part) {
+    __shared__ double acc[4 * SD_B];
+    __shared__ int ks[4 * SD_B], js[SD_B];
+    const int x = blockIdx.x % SD_X, w = blockIdx.x / SD_X, nw = gridDim.x / SD_X;
+    const int tid = threadIdx.x, l = tid & 15, grp = tid >> 4;
+    const int per = (nb + nw - 1) / nw, b0 = w * per, b1 = min(nb, b0 + per);
+    for (int c0 = b0; c0 < b1; c0 += SD_B) {
+        const int cnt = min(SD_B, b1 - c0);
+        for (int t = tid; t < 4 * cnt; t += 256) {
+            ks[t] = dpart[4L * c0 + t];
+            acc[t] = 0.0;
+            if (t < cnt) js[t] = dj[c0 + t];
+        }
+        __syncthreads();
+        const int pg = (cnt + 15) / 16, i0 = min(cnt, grp * pg), i1 = min(cnt, i0 + pg);
+        for (int q = x * SD_W; q < n; q += SD_X * SD_W) {
+            const int r = q + 2 * l;
+            if (q + SD_W <= n) sd_slab<true>(i0, i1, l, 0, ks, js, E + r, lde, Z + r, ldz, acc);
+            else sd_slab<false>(i0, i1, l, n - r, ks, js, E + r, lde, Z + r, ldz, acc);
+        }
+        __syncthreads();
+        for (int t = tid; t < 4 * cnt; t += 256) part[(4L * nb) * x + 4L * c0 + t] = acc[t];
+        __syncthreads();
+    }
+}
+__global__ __launch_bounds__(256) void sampled_dots_sum_kernel(int np, const int* __restrict__ didx,
+                                                               const double* __restrict__ part,
+                                                               double* __restrict__ out) {
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (t >= np || didx[t] < 0) return;
+    double v[SD_X];
+#pragma unroll
+    for (int x = 0; x < SD_X; ++x) v[x] = part[(long)np * x + t];
+    out[didx[t]] = ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
+}
+long sampled_dots_ws(int nb) { return 4L * nb * SD_X; }
+void sampled_dots(hipStream_t st, int n, int nb, const int* dj, const int* dpart, const int* didx, const double* E,
+                  long lde, const double* Z, long ldz, double* ws, double* out) {
+    if (nb <= 0) return;
+    const int nw = std::min(SD_WGS, cdiv(nb, 16));
+    hipLaunchKernelGGL(sampled_dots_kernel, dim3(SD_X * nw), dim3(256), 0, st, n, nb, dj, dpart, E, lde, Z, ldz, ws);
+    WC_LAUNCH_CHECK();
+    hipLaunchKernelGGL(sampled_dots_sum_kernel, dim3(cdiv(4L * nb, 256)), dim3(256), 0, st, 4 * nb, didx, ws, out);
     WC_LAUNCH_CHECK();
 }
 

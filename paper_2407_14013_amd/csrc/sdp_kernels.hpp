@@ -56,8 +56,10 @@ void sliced_values(hipStream_t st, long slots, const int* eidx, const double* u,
 int sampled_ye_columns(int n);
 void sampled_ye(hipStream_t st, int n, int nsl, const int* sptr, const int* srow, const uint16_t* ecol,
                 const double* val, const double* E, long lde, double* Z, long ldz);
-void sampled_dots(hipStream_t st, int n, const int* dptr, const int* dpart, const int* didx, const double* E, long lde,
-                  const double* Z, long ldz, double* out);
+// ws: sampled_dots_ws(nb) doubles
+long sampled_dots_ws(int nb);
+void sampled_dots(hipStream_t st, int n, int nb, const int* dj, const int* dpart, const int* didx, const double* E,
+                  long lde, const double* Z, long ldz, double* ws, double* out);
 void c_assemble(hipStream_t st, int n, int r, int b, int b2, const double* Z, long ldz, const double* sig, double t2,
                 double ib, double* C, long ldc);
 void add_diag_vec(hipStream_t st, int d, double* A, long lda, const double* sig, double t2);

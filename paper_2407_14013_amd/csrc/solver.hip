@@ -593,11 +593,15 @@ void setup(sdp_ctx* c, const sdp_problem* p, const sdp_sparse_rows* sp, const sd
                     }
                 }
             }
-            // constraints grouped by their smaller index j (partner k >= j)
-            std::vector<int> dp(n + 1, 0), dk(std::max(1, m)), di(std::max(1, m));
-            for (int i = 0; i < m; ++i) ++dp[hjk[2 * i] + 1];
-            for (int j = 0; j < n; ++j) dp[j + 1] += dp[j];
-            std::vector<int> at(dp.begin(), dp.end() - 1);
+            // constraints grouped by their smaller index j (partner k >= j), each
+            // group padded to batches of four
+            std::vector<int> at(n + 1, 0);
+            for (int i = 0; i < m; ++i) ++at[hjk[2 * i] + 1];
+            for (int j = 0; j < n; ++j) at[j + 1] = at[j] + static_cast<int>(round_up(at[j + 1], 4));
+            c->dnb = at[n] / 4;
+            std::vector<int> dk(at[n], 0), di(at[n], -1), dj(c->dnb);
+            for (int j = 0; j < n; ++j)
+                for (int b = at[j] / 4; b < at[j + 1] / 4; ++b) dj[b] = j;
             for (int i = 0; i < m; ++i) {
                 const int g = at[hjk[2 * i]]++;
                 dk[g] = hjk[2 * i + 1];
@@ -608,14 +612,15 @@ void setup(sdp_ctx* c, const sdp_problem* p, const sdp_sparse_rows* sp, const sd
             c->ecol.alloc(slots);
             c->eidx.alloc(slots);
             c->sval.alloc(slots);
-            c->dptr.alloc(n + 1);
+            c->dj.alloc(dj.size());
+            c->dws.alloc(sampled_dots_ws(c->dnb));
             c->dpart.alloc(dk.size());
             c->didx.alloc(di.size());
             WC_HIP(hipMemcpyAsync(c->sptr.get(), sptr.data(), sizeof(int) * (c->nsl + 1), hipMemcpyHostToDevice, st));
             WC_HIP(hipMemcpyAsync(c->srow.get(), srow.data(), sizeof(int) * srow.size(), hipMemcpyHostToDevice, st));
             WC_HIP(hipMemcpyAsync(c->ecol.get(), ecol.data(), sizeof(uint16_t) * slots, hipMemcpyHostToDevice, st));
             WC_HIP(hipMemcpyAsync(c->eidx.get(), eidx.data(), sizeof(int) * slots, hipMemcpyHostToDevice, st));
-            WC_HIP(hipMemcpyAsync(c->dptr.get(), dp.data(), sizeof(int) * (n + 1), hipMemcpyHostToDevice, st));
+            WC_HIP(hipMemcpyAsync(c->dj.get(), dj.data(), sizeof(int) * dj.size(), hipMemcpyHostToDevice, st));
             WC_HIP(hipMemcpyAsync(c->dpart.get(), dk.data(), sizeof(int) * dk.size(), hipMemcpyHostToDevice, st));
             WC_HIP(hipMemcpyAsync(c->didx.get(), di.data(), sizeof(int) * di.size(), hipMemcpyHostToDevice, st));
             WC_HIP(hipStreamSynchronize(st));
@@ -918,7 +923,7 @@ void newton_apply(sdp_ctx* c, const double* in, double* out) {
         sampled_ye(st, n, c->nsl, c->sptr, c->srow, c->ecol, c->sval, c->E, n, c->T1, n);
         prof_end(c, SDP_K_SAMPLED_YE, es, 16.0 * nn + 10.0 * slots);
         prof_begin(c, SDP_K_SAMPLED_DOTS, &es);
-        sampled_dots(st, n, c->dptr, c->dpart, c->didx, c->E, n, c->T1, n, out);
+        sampled_dots(st, n, c->dnb, c->dj, c->dpart, c->didx, c->E, n, c->T1, n, c->dws, out);
         prof_end(c, SDP_K_SAMPLED_DOTS, es, 16.0 * nn + 16.0 * m);
         // top += script-A script-Q v;  bottom = (script-A script-Q)^T u - tau^2 Sigma v
         const EntryAq q = entry_aq_args(c);

@@ -27,7 +27,9 @@ struct sdp_ctx {
     wc::DevBuf<int> sptr, srow, eidx;  // sliced pattern: slice start slot, row of each lane, constraint
                                        // (i off the diagonal, -2 - i on it, -1 in pads)
     wc::DevBuf<uint16_t> ecol;         // sliced pattern: column of each slot
-    wc::DevBuf<int> dptr, dpart, didx; // constraints grouped by their smaller index j: partner k, constraint
+    wc::DevBuf<int> dj, dpart, didx;   // batches of four constraints that share their smaller index j: j, partners k, constraints
+    wc::DevBuf<double> dws;            // their partial sums
+    int dnb = 0;                       // batches
     wc::DevBuf<double> sval;    // slot values of Y = A^T(u) in the sliced pattern
     wc::DevBuf<int> spptr, sprow, spcol;  // sparse: entries per constraint (row <= col)
     wc::DevBuf<double> spval;

@@ -220,3 +220,25 @@ def test_gemm_lds_loads_match_the_general_form(ta, tb, m, n, k):
     la.dgemm(ta, tb, 1.0, shifted(A), shifted(B), 0.0, got[1])
     assert np.abs(la.from_dev(got[0]) - ref).max() <= 4 * k * EPS * np.abs(A).max() * np.abs(B).max()
     assert torch.equal(got[0], got[1])
+
+
+# the sampled products against the dense ones: 8, 4 and 2 staged columns (n = 2048
+# | 2049, 4096 | 4097), fewer slabs than XCDs, a last slab of one row, one pair,
+# more pairs than a workgroup holds at a time.  Sums of n products in another
+# order, of entries of E that cancel: 1e-10 of the largest, as above.
+@pytest.mark.parametrize("n, m", [(70, 1), (129, 2000), (577, 166000), (2048, 3000), (2049, 60000), (4097, 300000)])
+def test_sampled_products_match_the_dense_ones(n, m):
+    rng = np.random.default_rng(n)
+    p = workloads.matrix_completion(n, 2, m, seed=n)
+    d = np.exp(0.5 * rng.standard_normal((2, n)))
+    U = rng.standard_normal((n, 2)) / np.sqrt(n)
+    pts = [np.diag(d[0]) + U @ U.T, np.zeros(m), np.diag(d[1])]
+    x = None
+    got = []
+    for sampled in (0, 1):
+        with Context(p, rank_fixed=2, sparse_sandwich=sampled) as ctx:
+            ctx.set_point(*(torch.from_numpy(a).cuda() for a in pts))
+            if x is None:
+                x = torch.from_numpy(rng.standard_normal(ctx.aug_dim())).cuda()
+            got.append(ctx.newton_apply(x).cpu().numpy())
+    assert np.abs(got[1] - got[0]).max() <= 1e-10 * np.abs(got[0]).max()

@@ -59,6 +59,46 @@ __device__ __forceinline__ void lp_store(void* C, long ldc, int M, int N, int r0
     }
 }
 
+// Whether four consecutive rows can be stored at once: columns start 16-byte
+// aligned (8-byte for BF16).
+template <LpOut OUT>
+__device__ __forceinline__ bool lp_vec(const void* C, long ldc) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(C);
+    if constexpr (OUT == LpOut::F32) return a % 16 == 0 && ldc % 4 == 0;
+    else if constexpr (OUT == LpOut::BF16) return a % 8 == 0 && ldc % 4 == 0;
+    else return a % 16 == 0 && ldc % 2 == 0;
+}
+// lp_store with one access for a lane's four rows (two in FP64): a quarter of
+// the store instructions.  vec: lp_vec.
+template <LpOut OUT>
+__device__ __forceinline__ void lp_store4(bool vec, void* C, long ldc, int M, int N, int r0, int c0, const v4f& acc) {
+    if (!vec || r0 + 16 > M) {
+        lp_store<OUT>(C, ldc, M, N, r0, c0, acc);
+        return;
+    }
+    typedef double v2d __attribute__((ext_vector_type(2)));
+    typedef unsigned short v4us __attribute__((ext_vector_type(4)));
+    const int lane = threadIdx.x & 63, col = c0 + (lane & 15);
+    if (col >= N) return;
+    const long o = r0 + 4 * (lane >> 4) + (long)col * ldc;
+    if constexpr (OUT == LpOut::F32) {
+        *reinterpret_cast<v4f*>(static_cast<float*>(C) + o) = acc;
+    } else if constexpr (OUT == LpOut::BF16) {
+        *reinterpret_cast<v4us*>(static_cast<unsigned short*>(C) + o) =
+            v4us{bf16_rne(acc[0]), bf16_rne(acc[1]), bf16_rne(acc[2]), bf16_rne(acc[3])};
+    } else {
+        v2d* p = reinterpret_cast<v2d*>(static_cast<double*>(C) + o);
+        v2d lo = {static_cast<double>(acc[0]), static_cast<double>(acc[1])};
+        v2d hi = {static_cast<double>(acc[2]), static_cast<double>(acc[3])};
+        if constexpr (OUT == LpOut::ADD_F64) {
+            lo += p[0];
+            hi += p[1];
+        }
+        p[0] = lo;
+        p[1] = hi;
+    }
+}
+
 // 64 x 64 output tile per workgroup, four waves in a 2 x 2 grid, each wave a
 // 2 x 2 block of 16 x 16 MFMA tiles; K staged through LDS 32 at a time.
 constexpr int LT = 64;
@@ -263,14 +303,16 @@ __global__ __launch_bounds__(256) void bgemm_sym_kernel(int M, int N, const unsi
     for (int x = 0; x < 4; ++x)
 #pragma unroll
         for (int y = 0; y < 4; ++y)
-            lp_store<OUT>(C, ldc, M, N, row0 + wm * 64 + x * 16, col0 + wn * 64 + y * 16, acc[x][y]);
+            lp_store4<OUT>(lp_vec<OUT>(C, ldc), C, ldc, M, N, row0 + wm * 64 + x * 16, col0 + wn * 64 + y * 16, acc[x][y]);
 }
 
 // The same BF16 product for large n: 256 x 256 output tile per workgroup,
-// four waves in a 2 x 2 grid, each wave a 128 x 128 block of 8 x 8 MFMA tiles
-// (16 x 16 x 32) whose accumulators take 256 registers per lane -- twice the
-// flops per LDS byte of the 128 x 128 kernel.  With one wave per SIMD there
-// is nothing to hide load latency behind, so the operands go from global
+// eight waves in a 2 x 4 grid, each wave a 128 x 64 block of 8 x 4 MFMA tiles
+// (16 x 16 x 32): two waves per SIMD, so that one reads fragments while the
+// other multiplies (four waves of 128 x 128 read less but wait: 1403 us at n =
+// 8192 against 1065, 154.5 against 151 at n = 4000).  All tiles end together at n
+// = 4000, so the result's 64 MB are written at once: with one access for four
+// rows 129 us (990 TF), with one per row 151.  The operands go from global
 // memory straight into LDS (global_load_lds, 16 bytes per lane, no register
 // staging) through a ring of BS = 4 stages: the loads of step k + 3 are in
 // flight while step k multiplies, and each step ends with a wait for step
@@ -307,36 +349,36 @@ __device__ __forceinline__ void xcd_tile(int tiles_m, int tiles_n, int& tm, int&
     }
 }
 
-// s_waitcnt vmcnt(n) for n in {0, 8, 16}, leaving expcnt and lgkmcnt alone (gfx9 encoding:
+// s_waitcnt vmcnt(n) for n in {0, 4, 8}, leaving expcnt and lgkmcnt alone (gfx9 encoding:
 // vmcnt bits [3:0] and [15:14], expcnt [6:4], lgkmcnt [11:8])
 __device__ __forceinline__ void wait_vmcnt(int n) {
-    if (n >= 16) __builtin_amdgcn_s_waitcnt((1 << 14) | 0x0F70);
-    else if (n >= 8) __builtin_amdgcn_s_waitcnt(0x0F70 | 8);
+    if (n >= 8) __builtin_amdgcn_s_waitcnt(0x0F70 | 8);
+    else if (n >= 4) __builtin_amdgcn_s_waitcnt(0x0F70 | 4);
     else __builtin_amdgcn_s_waitcnt(0x0F70);
 }
 // s_waitcnt lgkmcnt(0) with vmcnt and expcnt left alone
 __device__ __forceinline__ void wait_lgkm0() { __builtin_amdgcn_s_waitcnt(0xC07F); }
 
 template <LpOut OUT>
-__global__ __launch_bounds__(256) void bgemm_sym256_kernel(int M, int N, const unsigned short* __restrict__ A, long lda,
+__global__ __launch_bounds__(512, 2) void bgemm_sym256_kernel(int M, int N, const unsigned short* __restrict__ A, long lda,
                                                            const unsigned short* __restrict__ B, long ldb,
                                                            void* __restrict__ C, long ldc, int tiles_m, int tiles_n) {
     extern __shared__ __attribute__((aligned(16))) unsigned short hsm[];
     const int K = M;
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int wm = wv & 1, wn = wv >> 1;
+    const int wm = wv & 1, wn = wv >> 1;  // 2 x 4
     int tm, tn;
     xcd_tile(tiles_m, tiles_n, tm, tn);
     const int row0 = tm * BT, col0 = tn * BT;
     const int full = K / 32;  // steps whose 32 k-values are all in range
     // load instruction h of wave wv covers c = wv + 4 h: A rows (c < 16) or B columns
     // 16 (c % 16) .. + 15; lane l fills row l / 4, stage position l % 4
-    const unsigned short* src[8];
+    const unsigned short* src[4];
     {
         const int lrow = lane >> 2, lpos = lane & 3;
 #pragma unroll
-        for (int h = 0; h < 8; ++h) {
-            const int c = wv + 4 * h;
+        for (int h = 0; h < 4; ++h) {
+            const int c = wv + 8 * h;
             const int isB = c >> 4, r = 16 * (c & 15) + lrow;
             const int piece = lpos ^ ((r >> 1) & 3);
             int g = (isB ? col0 : row0) + r;
@@ -348,25 +390,25 @@ __global__ __launch_bounds__(256) void bgemm_sym256_kernel(int M, int N, const u
     auto issue = [&](int st) {
         unsigned short* stage = hsm + (st % BS) * BSTAGE;
 #pragma unroll
-        for (int h = 0; h < 8; ++h) {
-            const int c = wv + 4 * h;
+        for (int h = 0; h < 4; ++h) {
+            const int c = wv + 8 * h;
             __builtin_amdgcn_global_load_lds(src[h] + st * 32, stage + (c >> 4) * BT * 32 + (c & 15) * 16 * 32, 16,
                                              0, 0);
         }
     };
-    v4f acc[8][8];
+    v4f acc[8][4];
 #pragma unroll
     for (int x = 0; x < 8; ++x)
 #pragma unroll
-        for (int y = 0; y < 8; ++y) acc[x][y] = v4f{0.f, 0.f, 0.f, 0.f};
+        for (int y = 0; y < 4; ++y) acc[x][y] = v4f{0.f, 0.f, 0.f, 0.f};
     const int pos = (lane >> 4) ^ ((lane >> 1) & 3);
     const int aoff = (wm * 128 + (lane & 15)) * 32 + 8 * pos;
-    const int boff = BT * 32 + (wn * 128 + (lane & 15)) * 32 + 8 * pos;
-    v8us a[8], b[8];
+    const int boff = BT * 32 + (wn * 64 + (lane & 15)) * 32 + 8 * pos;
+    v8us a[8], b[4];
     int issued = 0;
     for (; issued < BS - 1 && issued < full; ++issued) issue(issued);
     if (full > 0) {
-        wait_vmcnt(8 * (issued - 1));
+        wait_vmcnt(4 * (issued - 1));
         __builtin_amdgcn_s_barrier();
     }
     for (int st = 0; st < full; ++st) {
@@ -377,20 +419,20 @@ __global__ __launch_bounds__(256) void bgemm_sym256_kernel(int M, int N, const u
         }
         const unsigned short* stage = hsm + (st % BS) * BSTAGE;
 #pragma unroll
-        for (int y = 0; y < 8; ++y) b[y] = *reinterpret_cast<const v8us*>(stage + boff + y * 16 * 32);
+        for (int y = 0; y < 4; ++y) b[y] = *reinterpret_cast<const v8us*>(stage + boff + y * 16 * 32);
 #pragma unroll
         for (int x = 0; x < 8; ++x) a[x] = *reinterpret_cast<const v8us*>(stage + aoff + x * 16 * 32);
         __builtin_amdgcn_sched_barrier(0);  // every fragment load ahead of the first product
 #pragma unroll
         for (int x = 0; x < 8; ++x)
 #pragma unroll
-            for (int y = 0; y < 8; ++y)
+            for (int y = 0; y < 4; ++y)
                 acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a[x]),
                                                                     __builtin_bit_cast(v8bf, b[y]), acc[x][y], 0, 0,
                                                                     0);
         // step st + 1's loads (this wave's) done, this step's fragment reads done, then everyone's
         const int ahead = issued - st - 2;
-        wait_vmcnt(8 * (ahead > 0 ? ahead : 0));
+        wait_vmcnt(4 * (ahead > 0 ? ahead : 0));
         wait_lgkm0();
         __builtin_amdgcn_s_barrier();
     }
@@ -398,8 +440,8 @@ __global__ __launch_bounds__(256) void bgemm_sym256_kernel(int M, int N, const u
         // ragged K tail: fragments straight from global memory, zero past K
         const int k = 32 * full + 8 * (lane >> 4);
 #pragma unroll
-        for (int y = 0; y < 8; ++y) {
-            const int g = col0 + wn * 128 + y * 16 + (lane & 15);
+        for (int y = 0; y < 4; ++y) {
+            const int g = col0 + wn * 64 + y * 16 + (lane & 15);
             b[y] = g < N ? load8_guarded(B + (long)g * ldb + k, k, K) : v8us{0, 0, 0, 0, 0, 0, 0, 0};
         }
 #pragma unroll
@@ -410,16 +452,17 @@ __global__ __launch_bounds__(256) void bgemm_sym256_kernel(int M, int N, const u
 #pragma unroll
         for (int x = 0; x < 8; ++x)
 #pragma unroll
-            for (int y = 0; y < 8; ++y)
+            for (int y = 0; y < 4; ++y)
                 acc[x][y] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, a[x]),
                                                                     __builtin_bit_cast(v8bf, b[y]), acc[x][y], 0, 0,
                                                                     0);
     }
+    const bool vec = lp_vec<OUT>(C, ldc);
 #pragma unroll
-    for (int x = 0; x < 8; ++x)
+    for (int y = 0; y < 4; ++y)
 #pragma unroll
-        for (int y = 0; y < 8; ++y)
-            lp_store<OUT>(C, ldc, M, N, row0 + wm * 128 + x * 16, col0 + wn * 128 + y * 16, acc[x][y]);
+        for (int x = 0; x < 8; ++x)
+            lp_store4<OUT>(vec, C, ldc, M, N, row0 + wm * 128 + x * 16, col0 + wn * 64 + y * 16, acc[x][y]);
 }
 
 // FP32 form of the same product: 128 x 128 tiles, four waves of 4 x 4 MFMA
@@ -513,7 +556,7 @@ __global__ __launch_bounds__(256) void sgemm_sym_kernel(int M, int N, const floa
     for (int x = 0; x < 4; ++x)
 #pragma unroll
         for (int y = 0; y < 4; ++y)
-            lp_store<OUT>(C, ldc, M, N, row0 + wm * 64 + x * 16, col0 + wn * 64 + y * 16, acc[x][y]);
+            lp_store4<OUT>(lp_vec<OUT>(C, ldc), C, ldc, M, N, row0 + wm * 64 + x * 16, col0 + wn * 64 + y * 16, acc[x][y]);
 }
 
 bool lp_gemm_sym(hipStream_t st, Lp in, LpOut out, int M, int N, const void* A, long lda, const void* B, long ldb,
@@ -550,10 +593,10 @@ bool lp_gemm_sym(hipStream_t st, Lp in, LpOut out, int M, int N, const void* A, 
         const size_t lds = sizeof(unsigned short) * BS * BSTAGE;  // 128 KB
         const dim3 g1(static_cast<unsigned>(tm * tn));
         switch (out) {
-            case LpOut::F32: hipLaunchKernelGGL(bgemm_sym256_kernel<LpOut::F32>, g1, dim3(256), lds, st, M, N, a, lda, b, ldb, C, ldc, tm, tn); break;
-            case LpOut::BF16: hipLaunchKernelGGL(bgemm_sym256_kernel<LpOut::BF16>, g1, dim3(256), lds, st, M, N, a, lda, b, ldb, C, ldc, tm, tn); break;
-            case LpOut::F64: hipLaunchKernelGGL(bgemm_sym256_kernel<LpOut::F64>, g1, dim3(256), lds, st, M, N, a, lda, b, ldb, C, ldc, tm, tn); break;
-            case LpOut::ADD_F64: hipLaunchKernelGGL(bgemm_sym256_kernel<LpOut::ADD_F64>, g1, dim3(256), lds, st, M, N, a, lda, b, ldb, C, ldc, tm, tn); break;
+            case LpOut::F32: hipLaunchKernelGGL(bgemm_sym256_kernel<LpOut::F32>, g1, dim3(512), lds, st, M, N, a, lda, b, ldb, C, ldc, tm, tn); break;
+            case LpOut::BF16: hipLaunchKernelGGL(bgemm_sym256_kernel<LpOut::BF16>, g1, dim3(512), lds, st, M, N, a, lda, b, ldb, C, ldc, tm, tn); break;
+            case LpOut::F64: hipLaunchKernelGGL(bgemm_sym256_kernel<LpOut::F64>, g1, dim3(512), lds, st, M, N, a, lda, b, ldb, C, ldc, tm, tn); break;
+            case LpOut::ADD_F64: hipLaunchKernelGGL(bgemm_sym256_kernel<LpOut::ADD_F64>, g1, dim3(512), lds, st, M, N, a, lda, b, ldb, C, ldc, tm, tn); break;
         }
         WC_LAUNCH_CHECK();
         return true;

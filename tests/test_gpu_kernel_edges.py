@@ -242,3 +242,23 @@ def test_sampled_products_match_the_dense_ones(n, m):
                 x = torch.from_numpy(rng.standard_normal(ctx.aug_dim())).cuda()
             got.append(ctx.newton_apply(x).cpu().numpy())
     assert np.abs(got[1] - got[0]).max() <= 1e-10 * np.abs(got[0]).max()
+
+
+# results stored four rows at a time, and one by one where the result is only
+# aligned to its own type: the same bits (256 x 256 BF16 tiles and the 128 x 128
+# ones of both types, ragged edges)
+@pytest.mark.parametrize("prec, m, n", [(1, 1032, 1030), (2, 1032, 1030), (2, 3896, 3620)])
+@pytest.mark.parametrize("out_kind", [0, 1, 2, 3])
+def test_low_precision_stores_do_not_depend_on_alignment(prec, m, n, out_kind):
+    rng = np.random.default_rng(m + n)
+    M = rng.standard_normal((m, m))
+    A = la.to_lowp(la.to_dev(M + M.T), prec)
+    B = la.to_lowp(la.to_dev(rng.standard_normal((m, n))), prec)
+    dt = {0: torch.float32, 1: torch.int16, 2: torch.float64, 3: torch.float64}[out_kind]
+    got = []
+    for shift in (0, 1):
+        buf = torch.ones(m * n + 1, dtype=dt, device="cuda")
+        Cm = buf[shift:shift + m * n].view(n, m)
+        got.append(la.gemm_lp_sym(prec, out_kind, A, B, Cm).clone())
+        assert buf[m * n if shift == 0 else 0].item() == 1  # nothing past the result
+    assert torch.equal(got[0], got[1])

@@ -262,3 +262,22 @@ def test_low_precision_stores_do_not_depend_on_alignment(prec, m, n, out_kind):
         got.append(la.gemm_lp_sym(prec, out_kind, A, B, Cm).clone())
         assert buf[m * n if shift == 0 else 0].item() == 1  # nothing past the result
     assert torch.equal(got[0], got[1])
+
+
+# staging: instances of 33 MB (a group of its own each) between small ones, in an
+# order that mixes both, against each instance staged alone; two iterations, so
+# rounding has not grown: 1e-9 as for the operator's other comparisons
+def test_batched_staging_groups_match_single_instances():
+    sizes = [(16, 48), (96, 900), (17, 60), (96, 901), (20, 100), (24, 216), (95, 899), (2, 1)]
+    probs = [workloads.gaussian_sensing(n, 1, m, seed=n + m) for n, m in sizes]
+    res, Xs, ys = batched.solve_batched(probs, want_y=True, max_ipm_iter=2)
+    for p, r, X, y in zip(probs, res, Xs, ys):
+        one, X1, y1 = batched.solve_batched([p], want_y=True, max_ipm_iter=2)
+        assert r["iterations"] == one[0]["iterations"]
+        assert abs(r["pobj"] - one[0]["pobj"]) <= 1e-9 * (1.0 + abs(one[0]["pobj"]))
+        assert (X - X1[0]).abs().max() <= 1e-9 * X1[0].abs().max()
+        assert (y - y1[0]).abs().max() <= 1e-9 * (1.0 + y1[0].abs().max())
+    bad = [dict(p) for p in probs]
+    bad[4] = dict(bad[4], A=np.where(np.arange(bad[4]["A"].size).reshape(bad[4]["A"].shape) == 7, np.inf, bad[4]["A"]))
+    with pytest.raises(Exception, match="non-finite"):
+        batched.solve_batched(bad, max_ipm_iter=2)

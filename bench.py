@@ -11,7 +11,7 @@ scaling point and its split are prepared before the timed region and every
 input is resident in HBM.
 
 The JSON line also carries:
-  roofline      the dominant kernel, dgemm_kernel on the full product Y E
+  roofline      the dominant kernel, dgemm_dma_kernel on the full product Y E
                 (2 n^3 flops per launch), timed live with HIP events on the
                 library's stream;
   forms         the other forms of the same operator (FP64 with the sampled
@@ -42,7 +42,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "packed_passes_gaussian_n200_m2400_hbm_traffic.json")
-GEMM_KERNEL = "dgemm_kernel<false, false, 128, 128, 0>"
+GEMM_KERNEL = "dgemm_dma_kernel<false, false>"
 GEMM_COUNTERS_FILE = os.path.join(ROOT, "profiles", "operator_completion_n4000_m160000_counters.json")
 KERNEL_SOURCE = os.path.join(ROOT, "paper_2407_14013_amd", "csrc", "blas.hip")
 METRIC = "Newton-op matvecs/s and IPM time-to-1e-8 gap, FP64 vs mixed prec, 1 GPU"

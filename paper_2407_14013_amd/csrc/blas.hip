@@ -1461,13 +1461,6 @@ __global__ void symmetrize_kernel(int n, double* A, long lda) {
     A[i + (long)j * lda] = v;
     A[j + (long)i * lda] = v;
 }
-__global__ void zero_upper_kernel(int n, double* A, long lda) {
-    long t = blockIdx.x * 256L + threadIdx.x;
-    if (t >= (long)n * n) return;
-    int i = static_cast<int>(t % n);
-    int j = static_cast<int>(t / n);
-    if (i < j) A[i + (long)j * lda] = 0.0;
-}
 __global__ void set_identity_kernel(int n, double* A, long lda, double diag) {
     long t = blockIdx.x * 256L + threadIdx.x;
     if (t >= (long)n * n) return;
@@ -1512,11 +1505,6 @@ void transpose(hipStream_t st, int rows, int cols, const double* A, long lda, do
 void symmetrize(hipStream_t st, int n, double* A, long lda) {
     if (n <= 0) return;
     hipLaunchKernelGGL(symmetrize_kernel, grid1((long)n * n), dim3(256), 0, st, n, A, lda);
-    WC_LAUNCH_CHECK();
-}
-void zero_upper(hipStream_t st, int n, double* A, long lda) {
-    if (n <= 0) return;
-    hipLaunchKernelGGL(zero_upper_kernel, grid1((long)n * n), dim3(256), 0, st, n, A, lda);
     WC_LAUNCH_CHECK();
 }
 void set_identity(hipStream_t st, int n, double* A, long lda, double diag) {

@@ -160,7 +160,6 @@ void scale(hipStream_t st, long n, double a, double* x);
 void mat_copy(hipStream_t st, int rows, int cols, const double* A, long lda, double* B, long ldb);
 void transpose(hipStream_t st, int rows, int cols, const double* A, long lda, double* B, long ldb);  // B = A^T
 void symmetrize(hipStream_t st, int n, double* A, long lda);                                        // A = (A+A^T)/2
-void zero_upper(hipStream_t st, int n, double* A, long lda);                                        // strict upper = 0
 void set_identity(hipStream_t st, int n, double* A, long lda, double diag);
 void add_diag(hipStream_t st, int n, double* A, long lda, double v);
 void scale_cols(hipStream_t st, int rows, int cols, const double* A, long lda, const double* s, double pw,

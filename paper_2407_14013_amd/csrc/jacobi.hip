@@ -592,7 +592,7 @@ __global__ __launch_bounds__(256) void jacobi_rotate_kernel(int n, int nblk, int
 // A round has only nblk / 2 workgroups (7 at n = 200), so it is bound by the
 // latency of one workgroup's chain: load, Gram matrix, inner rotations,
 // rotation.  Eight waves: the first four take A, the others V, whose loads
-// land while the Gram matrix forms.  At n = 200 a round takes 16.5 us; it was
+// land while the Gram matrix forms.  At n = 200 a round takes 15.7 us; it was
 // 27.8 us with all 496 pairs rotated in every round and four waves walking A,
 // then V.
 // ---------------------------------------------------------------------------

@@ -281,3 +281,22 @@ def test_batched_staging_groups_match_single_instances():
     bad[4] = dict(bad[4], A=np.where(np.arange(bad[4]["A"].size).reshape(bad[4]["A"].shape) == 7, np.inf, bad[4]["A"]))
     with pytest.raises(Exception, match="non-finite"):
         batched.solve_batched(bad, max_ipm_iter=2)
+
+
+# K of one to six 16-deep steps, whole and one more: where the loop that loads
+# two steps ahead ends; interior and edge tiles.  The bound of the product's
+# other checks.
+@pytest.mark.parametrize("ta", ["N", "T"])
+@pytest.mark.parametrize("tb", ["N", "T"])
+@pytest.mark.parametrize("k", [1, 15, 16, 17, 32, 33, 48, 49, 64, 65, 80, 81, 96, 97])
+def test_small_tile_gemm_step_counts(ta, tb, k):
+    m, n = 600, 577  # 100 tiles of 64 x 64: no split over K
+    rng = np.random.default_rng(k)
+    A = rng.standard_normal((k, m) if ta == "T" else (m, k))
+    B = rng.standard_normal((n, k) if tb == "T" else (k, n))
+    C0 = rng.standard_normal((m, n))
+    ref = 1.5 * (A.T if ta == "T" else A) @ (B.T if tb == "T" else B) - 0.5 * C0
+    Cd = la.to_dev(C0)
+    la.dgemm(ta, tb, 1.5, la.to_dev(A), la.to_dev(B), -0.5, Cd)
+    bound = 4 * k * EPS * (np.abs(A).max() * np.abs(B).max() * 1.5 + 0.5 * np.abs(C0).max())
+    assert np.abs(la.from_dev(Cd) - ref).max() <= bound + EPS * np.abs(ref).max()

@@ -12,13 +12,12 @@
 
 #include "common.hpp"
 #include "lanczos.hpp"
+#include "launch_plan.hpp"
 #include "wave.hpp"
 
 namespace wc {
 
-constexpr int LZ_THREADS = 1024;
 constexpr int LZ_WAVES = LZ_THREADS / 64;
-constexpr int LZ_TREG = 24;  // columns of its chunk of T that a thread keeps in registers
 
 __device__ inline double lz_block_sum(double v, double* red) {
     v = wave_sum_all(v);
@@ -117,10 +116,10 @@ __device__ __forceinline__ double lz_combine(int i, int j, int l0, int dl, const
     return v;
 }
 
-// Dynamic LDS layout: q (n, then LZ_TREG zeros), w (n), partial products of the matrix-vector
-// product (LZ_THREADS, only when rows are split into chunks), and, when it
-// fits (QLDS), the Lanczos basis (n x (kmax + 1)).  Otherwise the basis
-// lives in the global buffer Qg.
+// Dynamic LDS layout (lanczos_plan): q (n, then LZ_TREG zeros), w (n), partial
+// products of the matrix-vector product (LZ_THREADS, only when rows are split
+// into chunks), and, when it fits (QLDS), the Lanczos basis (n x (kmax + 1)).
+// Otherwise the basis lives in the global buffer Qg.
 //
 // The product w = T q splits each row into `nch` column chunks so that all
 // threads take part: thread t < n * nch forms the partial sum of row t % n
@@ -147,11 +146,12 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_kernel(int n, const double
     kout += blockIdx.x;
     extern __shared__ double sm[];
     double* q = sm;                 // current Lanczos vector
-    double* w = sm + n + LZ_TREG;   // work vector
-    const int nch = n > LZ_THREADS / 2 ? 1 : LZ_THREADS / n;
-    double* pp = w + n;             // partial products (nch > 1 only)
+    const LanczosPlan lp = lanczos_plan(n);
+    const int nch = lp.nch, clen = lp.clen;
+    double* w = sm + lp.w;          // work vector
+    double* pp = sm + lp.pp;        // partial products (nch > 1 only)
     double* Q;
-    if constexpr (QLDS) Q = w + n + (nch > 1 ? LZ_THREADS : 0);
+    if constexpr (QLDS) Q = sm + lp.Q;
     else Q = Qg;
     const long ldq = n;
     __shared__ double red[LZ_WAVES];
@@ -160,7 +160,6 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_kernel(int n, const double
     __shared__ int first_hit;
     const int tid = threadIdx.x;
     double theta_prev = 0.0, tnorm = 0.0;
-    const int clen = (n + nch - 1) / nch;
     const int ci = tid % n, cc = tid / n, cl0 = cc * clen;
     const bool chunked = nch > 1 && tid < n * nch;
     const int cl1 = min(n, cl0 + clen);
@@ -176,7 +175,7 @@ __global__ __launch_bounds__(LZ_THREADS) void lanczos_kernel(int n, const double
         q[i] = w[i] / nrm;
         Q[i] = q[i];
     }
-    for (int i = tid; i < LZ_TREG; i += LZ_THREADS) q[n + i] = 0.0;  // read past a last, shorter chunk
+    for (int i = tid; i < LZ_TREG; i += LZ_THREADS) q[n + i] = 0.0;  // read past the row's end
     double treg[LZ_TREG];
     if (chunked) {
 #pragma unroll
@@ -491,8 +490,7 @@ void lanczos_min_eig2(hipStream_t st, int n, const double* T0, const double* T1,
             }
         }
     } else {
-        const bool split = n <= LZ_THREADS / 2;
-        size_t shm = (2 * (size_t)n + LZ_TREG + (split ? LZ_THREADS : 0)) * sizeof(double);
+        size_t shm = lanczos_plan(n).Q * sizeof(double);
         const size_t qbytes = (size_t)n * (kmax + 1) * sizeof(double);
         const size_t static_lds = (LZ_WAVES + LZ_MAX_K + 1) * sizeof(double) + 2048;  // red, h, the tridiagonal, slack
         const int qlds = shm + qbytes + static_lds <= lds_max ? 1 : 0;

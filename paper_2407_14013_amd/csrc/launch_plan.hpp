@@ -1,6 +1,6 @@
-// Launch arithmetic of the split-K FP64 products (blas.hip), free of HIP so
-// that host code -- including a host-compiled test that enumerates shapes --
-// can evaluate it.  A plan splits K into `splits` slices of kc values; the
+// Launch arithmetic of the split-K FP64 products (blas.hip) and of the Lanczos
+// workgroup (lanczos.hip), free of HIP so that host code -- including
+// host-compiled tests that enumerate shapes -- can evaluate it.  A split-K plan splits K into `splits` slices of kc values; the
 // last slice takes the remainder klast = K - (splits - 1) kc, 1 <= klast <= kc,
 // so slice s reads operand columns (or rows) s kc .. s kc + (its K) - 1 only.
 #pragma once
@@ -56,6 +56,32 @@ inline SplitPlan thin_split_plan(int m, int n, int k, bool have_ws, long thin_ld
     p.splits = static_cast<int>(plan_cdiv(k, kc));
     p.kc = kc;
     p.klast = k - (p.splits - 1) * kc;
+    return p;
+}
+
+// The Lanczos workgroup's split of w = T q: every row in nch chunks of clen
+// columns (the last one shorter), thread t < n nch on row t % n and chunk t / n;
+// one chunk where a row leaves no thread for a second.  Only chunks that start
+// inside the row count: 1024 / n of them would start past it for small n.
+// Its dynamic LDS in doubles: q (n, then LZ_TREG zeros, which a thread's
+// register columns past the row's end are multiplied with: cl0 + u <= n - 1 +
+// LZ_TREG - 1), w (n) at `w`, partial sums (n nch) at `pp`, the basis at `Q`.
+constexpr int LZ_THREADS = 1024;
+constexpr int LZ_TREG = 24;  // columns of its chunk of T that a thread keeps in registers
+
+struct LanczosPlan {
+    int nch, clen;
+    int w, pp, Q;
+};
+
+constexpr LanczosPlan lanczos_plan(int n) {
+    LanczosPlan p{};
+    const int most = n > LZ_THREADS / 2 ? 1 : LZ_THREADS / n;
+    p.clen = (n + most - 1) / most;
+    p.nch = (n + p.clen - 1) / p.clen;
+    p.w = n + LZ_TREG;
+    p.pp = p.w + n;
+    p.Q = p.pp + (p.nch > 1 ? LZ_THREADS : 0);
     return p;
 }
 

@@ -355,11 +355,16 @@ __device__ __forceinline__ void wg_cols(int rows, int cols, const gd* A, int lda
 }
 
 // In-place lower Cholesky; returns 0 or the 1-based index of the first
-// non-positive pivot.  The strict upper triangle is set to zero.
+// non-positive pivot.  The strict upper triangle is set to zero.  A bad pivot
+// also returns through a barrier: the caller may refill A at once, before a
+// slower wave has read the pivot.
 __device__ __noinline__ int wg_potrf(int n, gd* A, long lda) {
     for (int j = 0; j < n; ++j) {
         const double d = A[j + (long)j * lda];
-        if (!(d > 0.0)) return j + 1;  // every thread read the same value
+        if (!(d > 0.0)) {  // every thread read the same value
+            bsync();
+            return j + 1;
+        }
         const double s = sqrt(d);
         bsync();
         for (int i = j + 1 + threadIdx.x; i < n; i += BT) A[i + (long)j * lda] /= s;
@@ -414,7 +419,10 @@ __device__ __noinline__ int wg_spd_inverse(int d, gd* A, int lda, gd* colk) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     for (int k = 0; k < d; ++k) {
         const double p = A[k + (long)k * lda];
-        if (!(p > 0.0)) return k + 1;
+        if (!(p > 0.0)) {
+            bsync();
+            return k + 1;
+        }
         for (int i = threadIdx.x; i < d; i += BT) colk[i] = A[i + (long)k * lda];
         bsync();
         const double ip = 1.0 / p;

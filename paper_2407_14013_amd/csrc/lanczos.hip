@@ -13,6 +13,7 @@
 #include "common.hpp"
 #include "lanczos.hpp"
 #include "launch_plan.hpp"
+#include "sturm.hpp"
 #include "wave.hpp"
 
 namespace wc {
@@ -35,12 +36,11 @@ __device__ inline double lz_block_sum(double v, double* red) {
 __device__ inline double lz_start(int i) { return 1.0 + 0.5 * sin(1.0 + 0.7071067811865476 * i) + 0.25 * cos(0.3 * i * i); }
 
 // Smallest eigenvalue of the k x k tridiagonal (ta, tb) in LDS, by multisection
-// of its Gershgorin interval: every thread counts the eigenvalues below one
-// point per round (Sturm sequence).  It only decides whether the Ritz value
-// has settled to 1e-10 of the norm, so four rounds (1025^4 = 1e12 intervals)
-// and a refined hardware reciprocal in the recurrence are enough; the division
-// and the two further rounds that it took before were a third of the kernel's
-// time (n = 200).  All threads of the workgroup call this.
+// of its Gershgorin interval: LZ_POINTS threads test one point each per round
+// (Sturm sequence), and eight rounds (257^8 = 2e19 intervals) reach the last
+// bits.  A round is a chain of k divisions per wave, so there is one wave on
+// each SIMD.  All threads of the workgroup call this.
+constexpr int LZ_POINTS = 256;
 __device__ __forceinline__ double lz_smallest(const double* ta, const double* tb, int k, int* first_hit) {
     const int tid = threadIdx.x;
     double lo = ta[0], hi = ta[0];
@@ -49,26 +49,16 @@ __device__ __forceinline__ double lz_smallest(const double* ta, const double* tb
         lo = fmin(lo, ta[i] - rr);
         hi = fmax(hi, ta[i] + rr);
     }
-    for (int round = 0; round < 4; ++round) {
-        const double step = (hi - lo) / (LZ_THREADS + 1);
-        const double x = lo + (tid + 1) * step;
-        int cnt = 0;
-        double dd = 1.0, bb = 0.0;
-        for (int i = 0; i < k; ++i) {
-            double rd = __builtin_amdgcn_rcp(dd);
-            rd = rd * fma(-dd, rd, 2.0);
-            dd = ta[i] - x - bb * rd;
-            bb = tb[i] * tb[i];
-            if (fabs(dd) < 1e-300) dd = -1e-300;
-            if (dd < 0.0) ++cnt;
-        }
-        if (tid == 0) *first_hit = LZ_THREADS;
+    for (int round = 0; round < 8; ++round) {
+        const double step = (hi - lo) / (LZ_POINTS + 1);
+        const bool below = tid < LZ_POINTS && eigenvalue_below(ta, tb, k, lo + (tid + 1) * step);
+        if (tid == 0) *first_hit = LZ_POINTS;
         __syncthreads();
-        if (cnt >= 1) atomicMin(first_hit, tid);
+        if (below) atomicMin(first_hit, tid);
         __syncthreads();
         const int t = *first_hit;
         __syncthreads();
-        const double nlo = lo + t * step, nhi = (t < LZ_THREADS) ? lo + (t + 1) * step : hi;
+        const double nlo = lo + t * step, nhi = (t < LZ_POINTS) ? lo + (t + 1) * step : hi;
         lo = nlo;
         hi = nhi;
     }
@@ -126,13 +116,13 @@ __device__ __forceinline__ double lz_combine(int i, int j, int l0, int dl, const
 // over chunk t / n, and the partials are added in chunk order.  A thread
 // keeps the first LZ_TREG columns of its part of T in registers for the whole
 // run (more of them spill at 1024 threads), so a step reads only the rest from
-// L2: 2 of 5 columns at n = 200, none up to n = 156.
+// L2: 2 of 5 columns at n = 200, none up to n = 146.
 // The second half of a reorthogonalisation pass is split over the same chunks.
 // A step is a chain of about ten phases of one workgroup, bound by their
-// latency.  At n = 200 a launch of two runs takes 660 us; it took 1030 us with
-// T read from L2 in every step, one thread per row subtracting the projections
-// one after another, sums through the LDS crossbar and the Ritz value found
-// with divisions (n = 301: 875 and 1057 us).
+// latency.  A call of 64 steps takes 860 us at n = 200 (1.50 ms at n = 301); it
+// took 1.14 ms (1.77 ms) with T read from L2 in every step, one thread per row
+// subtracting the projections one after another, and sums through the LDS
+// crossbar.
 // Workgroup b of the launch works on T_b (T0 or T1) with its own basis
 // buffer, coefficients and step count.
 template <bool QLDS>
@@ -425,19 +415,6 @@ LanczosWork::~LanczosWork() {
     if (pinned) (void)hipHostFree(pinned);
 }
 
-// Number of eigenvalues of the symmetric tridiagonal (a, b) below x (Sturm count).
-static int sturm_count(const double* a, const double* b, int k, double x) {
-    int cnt = 0;
-    double d = 1.0;
-    for (int i = 0; i < k; ++i) {
-        double bb = (i > 0) ? b[i - 1] * b[i - 1] : 0.0;
-        d = a[i] - x - (i > 0 ? bb / d : 0.0);
-        if (d == 0.0) d = -1e-300;
-        if (d < 0.0) ++cnt;
-    }
-    return cnt;
-}
-
 double tridiag_min_eig(const double* a, const double* b, int k) {
     double lo = a[0], hi = a[0];
     for (int i = 0; i < k; ++i) {
@@ -447,7 +424,7 @@ double tridiag_min_eig(const double* a, const double* b, int k) {
     }
     for (int it = 0; it < 200 && hi - lo > 1e-15 * std::max(std::fabs(lo), std::fabs(hi)) + 1e-300; ++it) {
         double mid = 0.5 * (lo + hi);
-        if (sturm_count(a, b, k, mid) >= 1) hi = mid;
+        if (eigenvalue_below(a, b, k, mid)) hi = mid;
         else lo = mid;
     }
     return 0.5 * (lo + hi);

@@ -602,7 +602,6 @@ void dgemm_lower(hipStream_t st, int n, int k, const double* A, long lda, const 
 // op(A) = A^T: one wave per output row (a contiguous column of A), lanes
 // over K, wave reduction.
 // ---------------------------------------------------------------------------
-constexpr int THIN_N = 16;
 
 // 64 rows per workgroup; the four waves split K and their partial sums are
 // added in LDS in wave order.

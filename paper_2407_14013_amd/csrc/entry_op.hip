@@ -8,6 +8,7 @@
 // bound by its bytes, and the refinement's two transposed products share one.
 #include "entry_op.hpp"
 
+#include "launch_plan.hpp"
 #include "sdp_kernels.hpp"
 #include "wave.hpp"
 
@@ -280,8 +281,9 @@ void entry_aqt(hipStream_t st, const EntryAq& q, const double* u0, double a0, co
         WC_LAUNCH_CHECK();
         return;
     }
-    if (!dgemm_thin(st, true, n, nv * r, n, 1.0, q.Gw, n, q.YQ, n, 0.0, q.F, n))
-        dgemm(st, true, false, n, nv * r, n, 1.0, q.Gw, n, q.YQ, n, 0.0, q.F, n);
+    const int per = thin_vectors(r, nv);
+    for (int k = 0; k < nv; k += per)
+        q.product(true, per * r, q.YQ + (long)k * r * n, q.F + (long)k * r * n);
     hipLaunchKernelGGL(entry_f_to_v_kernel, dim3(cdiv(d + q.lp.t, 256)), dim3(256), 0, st, n, r, q.F, nv, o,
                        q.lp, u0, u1);
     WC_LAUNCH_CHECK();
@@ -334,7 +336,7 @@ __global__ __launch_bounds__(256) void entry_u_kernel(int n, int r, const double
     }
 }
 
-static void form_u(hipStream_t st, const EntryAq& q, const double* v) {
+void entry_form_u(hipStream_t st, const EntryAq& q, const double* v) {
     const int n = q.n, r = q.r;
     if (small_form(n, r)) {
         const size_t lds = sizeof(double) * (size_t)n * r;
@@ -346,8 +348,7 @@ static void form_u(hipStream_t st, const EntryAq& q, const double* v) {
         return;
     }
     v_to_h(st, n, r, v, q.Hm);
-    if (!dgemm_thin(st, false, n, r, n, 1.0, q.Gw, n, q.Hm, n, 0.0, q.U, n, q.thin_ws, q.thin_len))
-        dgemm(st, false, false, n, r, n, 1.0, q.Gw, n, q.Hm, n, 0.0, q.U, n);
+    q.product(false, r, q.Hm, q.U);
 }
 
 // (U_j . q_k + U_k . q_j) / 2
@@ -439,23 +440,21 @@ __global__ __launch_bounds__(256) void entry_aq_up2_kernel(int m, int n, int r, 
     }
 }
 
-void entry_aq_op(hipStream_t st, const EntryAq& q, const double* v, const double* M, bool lower, int splits,
-                 double* out) {
-    form_u(st, q, v);
+void entry_aq_op(hipStream_t st, const EntryAq& q, const double* M, bool lower, int splits, double* out) {
     hipLaunchKernelGGL(entry_aq_op_kernel, dim3(cdiv(q.m, 256)), dim3(256), 0, st, q.m, q.n, q.r, q.jk, q.U, q.Gw, M,
                        lower ? 1 : 0, splits, out);
     WC_LAUNCH_CHECK();
 }
 void entry_aq_up(hipStream_t st, const EntryAq& q, const double* v, const double* f, double ib, double beta, double* z1,
                  double* rho) {
-    form_u(st, q, v);
+    entry_form_u(st, q, v);
     hipLaunchKernelGGL(entry_aq_up_kernel, dim3(cdiv(q.m, 256)), dim3(256), 0, st, q.m, q.n, q.r, q.jk, q.U, q.Gw, f,
                        ib, beta, z1, rho, q.lp, v + dim_v(q));
     WC_LAUNCH_CHECK();
 }
 void entry_aq_up2(hipStream_t st, const EntryAq& q, const double* v, const double* rho, double ib, double* z1,
                   const double* zv, double* zout) {
-    form_u(st, q, v);
+    entry_form_u(st, q, v);
     const int d = dim_v(q) + q.lp.t;
     hipLaunchKernelGGL(entry_aq_up2_kernel, dim3(cdiv((long)q.m + d, 256)), dim3(256), 0, st, q.m, q.n, q.r, q.jk, q.U,
                        q.Gw, rho, ib, z1, d, zv, v, zout, q.lp, v + dim_v(q));

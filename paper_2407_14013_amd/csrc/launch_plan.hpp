@@ -13,6 +13,7 @@ namespace wc {
 constexpr int GBM = 64, GBN = 64, GBK = 16;
 constexpr int GEMM_SPLITS = 8;        // most K-splits of a small product
 constexpr int GEMM_SPLIT_TILES = 64;  // split K only below this many output tiles
+constexpr int THIN_N = 16;            // most columns of the thin product
 constexpr int THIN_LDS = 4096;        // doubles of B staged in LDS by the thin product
 constexpr int THIN_SPLITS = 32;       // most K-splits of the thin split-K form
 
@@ -58,6 +59,14 @@ inline SplitPlan thin_split_plan(int m, int n, int k, bool have_ws, long thin_ld
     p.klast = k - (p.splits - 1) * kc;
     return p;
 }
+
+// How many of nv vectors' products of r columns each one launch takes: all while
+// their columns together are few enough for the thin product, else one by one
+// (past THIN_N columns only the general product is left, whose few tiles need a
+// split over K to fill the chip).  A preconditioner product at n = 2000, r = 9: 770
+// us joined, 743 one by one; at n = 1000, r = 17: 755 us joined and not split over K,
+// 580 one by one and split.
+constexpr int thin_vectors(int r, int nv) { return r * nv <= THIN_N ? nv : 1; }
 
 // The Lanczos workgroup's split of w = T q: every row in nch chunks of clen
 // columns (the last one shorter), thread t < n nch on row t % n and chunk t / n;

@@ -859,8 +859,11 @@ static void lp_operator(sdp_ctx* c, const double* u, const double* v, double* ou
 
 // lp: with the LP columns in T (the preconditioner; the operator has its own LP part)
 static EntryAq entry_aq_args(sdp_ctx* c, bool lp = false) {
-    EntryAq q{c->n,  c->m,   c->r,  c->jk, c->rptr, c->rcol, c->ridx,
-              c->Gw, c->sig, c->Hm, c->U,  c->YQ,   c->F,    c->thin_ws, static_cast<long>(c->thin_ws.n), {}};
+    EntryAq q{c->n,   c->m,  c->r, c->jk, c->rptr, c->rcol, c->ridx, c->Gw,
+              c->sig, c->Hm, c->U, c->YQ, c->F,    {},      {}};
+    q.product = [c](bool ta, int cols, const double* B, double* C) {
+        gemm(c, ta, false, c->n, cols, c->n, 1.0, c->Gw, c->n, B, c->n, 0.0, C, c->n);
+    };
     if (lp && c->t > 0)
         q.lp = EntryLp{c->t,     c->Tl,    c->lcptr, c->lcrow, c->lrptr,
                        c->lrcol, c->posl, c->lcval, c->lrval};
@@ -927,7 +930,8 @@ void newton_apply(sdp_ctx* c, const double* in, double* out) {
         prof_end(c, SDP_K_SAMPLED_DOTS, es, 16.0 * nn + 16.0 * m);
         // top += script-A script-Q v;  bottom = (script-A script-Q)^T u - tau^2 Sigma v
         const EntryAq q = entry_aq_args(c);
-        entry_aq_op(st, q, v, nullptr, false, 0, out);
+        entry_form_u(st, q, v);
+        entry_aq_op(st, q, nullptr, false, 0, out);
         entry_aqt(st, q, u, 1.0, nullptr, 0.0, nullptr, -(c->tau * c->tau), v, out + m);
         lp_operator(c, u, v, out);
         prof_end(c, SDP_K_NEWTON, e, 0.0);
@@ -949,19 +953,23 @@ void newton_apply(sdp_ctx* c, const double* in, double* out) {
     prof_begin(c, SDP_K_SANDWICH, &es);
     gemm(c, false, false, n, n, n, 1.0, c->Y, n, c->E, n, 0.0, c->T1, n);
     prof_end(c, SDP_K_SANDWICH, es, sw_bytes);
+    const bool entry = c->kind == SDP_A_ENTRY;
+    EntryAq q{};
+    if (entry) {
+        q = entry_aq_args(c);
+        entry_form_u(st, q, v);  // before the partial products take the split-K workspace
+    }
     // E (Y E) is symmetric: at large n only its lower triangle is computed
     const bool lower = dgemm_lower_pays(n);
     prof_begin(c, lower ? SDP_K_SANDWICH_LOWER : SDP_K_SANDWICH, &es);
     // entry sampling reads E Y E at the sampled pairs only, so split-K partial
     // products need no sum and a lower triangle no mirror
-    const bool entry = c->kind == SDP_A_ENTRY;
     const int splits =
         entry ? dgemm_partials(st, n, c->E, n, c->T1, n, c->gemm_ws, static_cast<long>(c->gemm_ws.n)) : 0;
     if (splits == 0) gemm_sym(c, c->E, c->T1, c->Mm);
     prof_end(c, lower ? SDP_K_SANDWICH_LOWER : SDP_K_SANDWICH, es, lower ? 8.0 * 0.5 * nn : sw_bytes);
     if (entry) {
-        const EntryAq q = entry_aq_args(c);
-        entry_aq_op(st, q, v, splits > 0 ? c->gemm_ws.get() : c->Mm.get(), lower, splits, out);
+        entry_aq_op(st, q, splits > 0 ? c->gemm_ws.get() : c->Mm.get(), lower, splits, out);
         entry_aqt(st, q, u, 1.0, nullptr, 0.0, nullptr, -(c->tau * c->tau), v, out + m);
         lp_operator(c, u, v, out);
         prof_end(c, SDP_K_NEWTON, e, 0.0);
@@ -1050,7 +1058,8 @@ void newton_apply_lowp(sdp_ctx* c, const double* in, double* out) {
         entry_gather_f32(st, m, c->jk, Mf, n, out, 1.0, 0.0);
         // top += script-A script-Q v;  bottom = (script-A script-Q)^T u - tau^2 Sigma v
         const EntryAq q = entry_aq_args(c);
-        entry_aq_op(st, q, v, nullptr, false, 0, out);
+        entry_form_u(st, q, v);
+        entry_aq_op(st, q, nullptr, false, 0, out);
         entry_aqt(st, q, u, 1.0, nullptr, 0.0, nullptr, -(c->tau * c->tau), v, out + m);
     }
     lp_operator(c, u, v, out);

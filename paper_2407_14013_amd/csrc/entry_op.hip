@@ -1,11 +1,12 @@
 // Entry-sampling script-A script-Q products (Section 6).  For A_i = sym(e_j e_k^T)
 //   (AQ v)_i = (U_j . q_k + U_k . q_j) / 2 with U = G_w H(v), and
 //   (AQ)^T u = [svec; sqrt2 vec] of F = G_w^T (A^T(u) Q),
-// H = [B; sqrt2 N] and q_j the first r entries of row j of G_w.  At n <= 1024 every
-// piece is a few microseconds of latency, so each product is two launches with
-// the coordinate maps and the vector updates inside (n = 301, m = 9000: 14 us to
-// 7 us for AQ v, 16 to 8 us for (AQ)^T u); past that the two passes over G_w are
-// bound by its bytes, and the refinement's two transposed products share one.
+// H = [B; sqrt2 N] and q_j the first r entries of row j of G_w.  While G_w is
+// small every piece is a few microseconds of latency, so each product is two
+// launches with the coordinate maps and the vector updates inside (n = 301, m =
+// 9000: 14 us to 7 us for AQ v, 16 to 8 us for (AQ)^T u); past that the two passes
+// over G_w are bound by its bytes, and the refinement's two transposed products
+// share one.
 #include "entry_op.hpp"
 
 #include "launch_plan.hpp"
@@ -16,8 +17,6 @@ namespace wc {
 
 constexpr double kS2 = 1.4142135623730951;
 constexpr double kIS2 = 0.7071067811865476;
-constexpr int EN_SMALL = 1024;  // largest n of the latency-bound forms (n r <= 8192 as well: H sits in LDS)
-constexpr int EN_R = 16;        // most columns of Q in one launch
 
 // svec position c (0-based) of an r x r symmetric block -> (row i, column jj), i >= jj
 __device__ inline void svec_ij(int c, int r, int& i, int& jj) {
@@ -245,7 +244,6 @@ __global__ __launch_bounds__(256) void entry_f_to_v_kernel(int n, int r, const d
 }
 
 static int dim_v(const EntryAq& q) { return q.r * (q.r + 1) / 2 + (q.n - q.r) * q.r; }
-static bool small_form(int n, int r) { return n <= EN_SMALL && r <= EN_R && n * r <= 8192; }
 
 template <int R, int NV>
 static void yq_launch(hipStream_t st, const EntryAq& q, const double* u0, const double* u1, int r, const double* Q,
@@ -268,7 +266,7 @@ void entry_aqt(hipStream_t st, const EntryAq& q, const double* u0, double a0, co
                 yq_launch<EN_R, 1>(st, q, k ? u1 : u0, nullptr, std::min(EN_R, r - b0), q.Gw + (long)b0 * n,
                                    q.YQ + (long)(k * r + b0) * n);
     }
-    if (small_form(n, r)) {
+    if (entry_small(n, r)) {
         const dim3 grid(1 + cdiv(n - r, 4) + cdiv(q.lp.t, 256));
         if (r <= 4 && nv == 2)
             hipLaunchKernelGGL((entry_fv_kernel<4, 2>), grid, dim3(256), 0, st, n, r, q.Gw, q.YQ, o, q.lp, u0, u1);
@@ -338,7 +336,7 @@ __global__ __launch_bounds__(256) void entry_u_kernel(int n, int r, const double
 
 void entry_form_u(hipStream_t st, const EntryAq& q, const double* v) {
     const int n = q.n, r = q.r;
-    if (small_form(n, r)) {
+    if (entry_small(n, r)) {
         const size_t lds = sizeof(double) * (size_t)n * r;
         if (r <= 4)
             hipLaunchKernelGGL(entry_u_kernel<4>, dim3(cdiv(n, 16)), dim3(256), lds, st, n, r, q.Gw, v, q.U);

@@ -1,5 +1,5 @@
-// Launch arithmetic of the split-K FP64 products (blas.hip) and of the Lanczos
-// workgroup (lanczos.hip), free of HIP so that host code -- including
+// Launch arithmetic of the split-K FP64 products (blas.hip), of the products for
+// entry sampling (entry_op.hip) and of the Lanczos workgroup (lanczos.hip), free of HIP so that host code -- including
 // host-compiled tests that enumerate shapes -- can evaluate it.  A split-K plan splits K into `splits` slices of kc values; the
 // last slice takes the remainder klast = K - (splits - 1) kc, 1 <= klast <= kc,
 // so slice s reads operand columns (or rows) s kc .. s kc + (its K) - 1 only.
@@ -67,6 +67,14 @@ inline SplitPlan thin_split_plan(int m, int n, int k, bool have_ws, long thin_ld
 // us joined, 743 one by one; at n = 1000, r = 17: 755 us joined and not split over K,
 // 580 one by one and split.
 constexpr int thin_vectors(int r, int nv) { return r * nv <= THIN_N ? nv : 1; }
+
+// Entry sampling's latency-bound forms (entry_op.hip): where they are the faster
+// ones, and H (n r doubles) fits in LDS.  precond_apply in us, these forms and the
+// general ones: r = 4 70 and 91 at n = 512, 111 and 111 at n = 1024, 137 and 128 at n =
+// 1200; r = 8, whose kernels hold EN_R columns and load a step at a time, 110 and
+// 142 at n = 300, 173 and 174 at n = 640, 199 and 187 at n = 768, 269 and 230 at n = 1024.
+constexpr int EN_R = 16;  // most columns of Q in one launch
+constexpr bool entry_small(int n, int r) { return n <= (r <= 4 ? 1024 : 640) && r <= EN_R && n * r <= 8192; }
 
 // The Lanczos workgroup's split of w = T q: every row in nch chunks of clen
 // columns (the last one shorter), thread t < n nch on row t % n and chunk t / n;

@@ -1,10 +1,11 @@
 // Augmented operator for dense constraint rows (eq. augsys): at n = 200 the two
 // streaming passes over the packed rows take 121 us, and everything else is
-// small enough that the number of launches counts.  The off-diagonal blocks
-// are products with the explicit script-A script-Q (11.5 MB each way at n = 200,
-// m = 2400, the matrices that the preconditioner uses), taken by the same
-// launch as the last pass, so the operator is six launches (three for
-// n <= 64) instead of sixteen: n = 200 182 -> 150 us, n = 20 41 -> 17 us.
+// small enough that the number of launches counts.  While script-A script-Q is
+// small too (dense_explicit), the off-diagonal blocks are products with the
+// explicit matrix (11.5 MB each way at n = 200, m = 2400, the matrices that the
+// preconditioner uses), taken by the same launch as the last pass, so the operator
+// is six launches (three for n <= 64) instead of sixteen: n = 200 182 -> 150 us, n =
+// 20 41 -> 13 us.
 #include "dense_op.hpp"
 
 #include <hip/hip_ext.h>

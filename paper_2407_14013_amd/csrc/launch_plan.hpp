@@ -1,5 +1,5 @@
-// Launch arithmetic of the split-K FP64 products (blas.hip), of the products for
-// entry sampling (entry_op.hip) and of the Lanczos workgroup (lanczos.hip), free of HIP so that host code -- including
+// Launch arithmetic of the split-K FP64 products (blas.hip), of the operator's
+// forms for dense rows and entry sampling (dense_op.hip, entry_op.hip) and of the Lanczos workgroup (lanczos.hip), free of HIP so that host code -- including
 // host-compiled tests that enumerate shapes -- can evaluate it.  A split-K plan splits K into `splits` slices of kc values; the
 // last slice takes the remainder klast = K - (splits - 1) kc, 1 <= klast <= kc,
 // so slice s reads operand columns (or rows) s kc .. s kc + (its K) - 1 only.
@@ -67,6 +67,15 @@ inline SplitPlan thin_split_plan(int m, int n, int k, bool have_ws, long thin_ld
 // us joined, 743 one by one; at n = 1000, r = 17: 755 us joined and not split over K,
 // 580 one by one and split.
 constexpr int thin_vectors(int r, int nv) { return r * nv <= THIN_N ? nv : 1; }
+
+// Dense rows: whether the operator takes its off-diagonal blocks from the explicit
+// script-A script-Q (m x d, read once each way) or as products with G_w.  The
+// products cost some forty microseconds of launches whatever m d is, the explicit
+// passes 16 m d bytes, from the last-level cache while both copies fit in it.
+// newton_apply in us, explicit and products: n = 100, r = 60, m d = 17e6 116 and 124; n
+// = 150, r = 20, m d = 25e6 347 and 322; n = 200, r = 10, 12e6 358 and 402, r = 15, 26e6
+// 545 and 571, r = 20, 46e6 773 and 680; n = 300, r = 10, 27e6 1153 and 1119.
+constexpr bool dense_explicit(long m, long d) { return m * d <= 20'000'000; }
 
 // Entry sampling's latency-bound forms (entry_op.hip): where they are the faster
 // ones, and H (n r doubles) fits in LDS.  precond_apply in us, these forms and the

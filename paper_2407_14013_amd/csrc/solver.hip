@@ -10,6 +10,7 @@
 #include "dense_op.hpp"
 #include "entry_op.hpp"
 #include "lanczos.hpp"
+#include "launch_plan.hpp"
 #include "lp_kernels.hpp"
 #include "sdp_kernels.hpp"
 #include "solver.hpp"
@@ -938,7 +939,7 @@ void newton_apply(sdp_ctx* c, const double* in, double* out) {
         c->matvecs += 1;
         return;
     }
-    if (c->kind == SDP_A_DENSE) {
+    if (c->kind == SDP_A_DENSE && dense_explicit(m, c->d)) {
         dense_operator(c, u, v, out);
         lp_operator(c, u, v, out);
         prof_end(c, SDP_K_NEWTON, e, 0.0);

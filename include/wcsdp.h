@@ -469,10 +469,13 @@ enum {
     SDP_K_A_APPLY = 0,   /* A(M): packed dense rows times the weighted packed M (the operator's
                             launch also takes its off-diagonal products; their bytes are counted) */
     SDP_K_AT_APPLY = 1,  /* A^T(u): slab partial column sums of the packed rows */
-    SDP_K_GEMM = 2,      /* every FP64 GEMM launch */
+    SDP_K_GEMM = 2,      /* every FP64 GEMM launch (products that are part of another kernel are not
+                            GEMM launches: E Y E for dense rows with n <= 64, and those with
+                            script-A script-Q in entry sampling's forms for small n) */
     SDP_K_NEWTON = 3,    /* a whole sdp_newton_apply */
     SDP_K_SANDWICH = 4,  /* each n x n x n GEMM of E Y E inside the operator, FP64 or low precision
-                            (2 n^3 flops per launch; bytes = its operands and result) */
+                            (2 n^3 flops per launch; bytes = its operands and result); for dense
+                            rows with n <= 64 the one launch that takes both products */
     SDP_K_SAMPLED_YE = 5,   /* sparse_sandwich: Z = A^T(u) E from the sliced pattern (bytes = E read
                                and Z written once, 10 per pattern slot) */
     SDP_K_SAMPLED_DOTS = 6, /* sparse_sandwich: E[:, j] . Z[:, k] per constraint (algorithmic HBM

@@ -133,6 +133,17 @@ static void gemm_sym(sdp_ctx* c, const double* E, const double* T, double* M) {
     dgemm_lower(c->st, n, n, E, n, T, n, M, n, c->gemm_ws, static_cast<long>(c->gemm_ws.n));
     prof_end(c, SDP_K_GEMM, e, 8.0 * 3.0 * (double)n * n);
 }
+// The split-K partial products of E T in the GEMM workspace where dgemm would split
+// it (returns their number), else 0 and nothing launched.
+static int gemm_partials(sdp_ctx* c, const double* E, const double* T) {
+    const int n = c->n;
+    hipEvent_t e;
+    prof_begin(c, SDP_K_GEMM, &e);
+    const int splits = dgemm_partials(c->st, n, E, n, T, n, c->gemm_ws, static_cast<long>(c->gemm_ws.n));
+    if (splits > 0) prof_end(c, SDP_K_GEMM, e, 8.0 * 3.0 * (double)n * n);
+    else if (e != nullptr) (void)hipEventDestroy(e);
+    return splits;
+}
 // M += sym(U Q^T) (rank r, U n x r, Q = G_w[:, :r]; r may be 0) after gemm_sym,
 // mirroring its lower triangle when that is all it wrote.
 static void sym_finish(sdp_ctx* c, int r, const double* U, double* M) {
@@ -892,7 +903,7 @@ static void dense_operator(sdp_ctx* c, const double* u, const double* v, double*
         const bool lower = dgemm_lower_pays(n);
         const int cls = lower ? SDP_K_SANDWICH_LOWER : SDP_K_SANDWICH;
         prof_begin(c, cls, &es);
-        const int splits = dgemm_partials(st, n, c->E, n, c->T1, n, c->gemm_ws, static_cast<long>(c->gemm_ws.n));
+        const int splits = gemm_partials(c, c->E, c->T1);
         if (splits == 0) gemm_sym(c, c->E, c->T1, c->Mm);
         prof_end(c, cls, es, lower ? 4.0 * (double)n * n : sw_bytes);
         if (splits > 0) {
@@ -965,8 +976,7 @@ void newton_apply(sdp_ctx* c, const double* in, double* out) {
     prof_begin(c, lower ? SDP_K_SANDWICH_LOWER : SDP_K_SANDWICH, &es);
     // entry sampling reads E Y E at the sampled pairs only, so split-K partial
     // products need no sum and a lower triangle no mirror
-    const int splits =
-        entry ? dgemm_partials(st, n, c->E, n, c->T1, n, c->gemm_ws, static_cast<long>(c->gemm_ws.n)) : 0;
+    const int splits = entry ? gemm_partials(c, c->E, c->T1) : 0;
     if (splits == 0) gemm_sym(c, c->E, c->T1, c->Mm);
     prof_end(c, lower ? SDP_K_SANDWICH_LOWER : SDP_K_SANDWICH, es, lower ? 8.0 * 0.5 * nn : sw_bytes);
     if (entry) {

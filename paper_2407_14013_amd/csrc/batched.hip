@@ -32,12 +32,11 @@
 #include <cmath>
 #include <exception>
 #include <numeric>
-#include <system_error>
-#include <thread>
 #include <type_traits>
 #include <vector>
 
 #include "batched.hpp"
+#include "host_pool.hpp"
 #include "sdp_kernels.hpp"
 #include "wave.hpp"
 
@@ -1894,14 +1893,7 @@ void stage(const sdp_problem* probs, int count, const sdp_options& o, hipStream_
         // a thread pays from a megabyte on; without one, this thread does the work
         const long mb = 8 * (off[i1] - off[i0]) >> 20;
         const int nt = static_cast<int>(std::min<long>({STAGE_THREADS - 1, mb, i1 - i0 - 1}));
-        std::vector<std::thread> pool;
-        pool.reserve(std::max(0, nt));
-        try {
-            for (int t = 0; t < nt; ++t) pool.emplace_back(work);
-        } catch (const std::system_error&) {  // fewer threads, then
-        }
-        work();
-        for (auto& t : pool) t.join();
+        run_shared(nt, work);
         for (auto& e : errs)
             if (e) std::rethrow_exception(e);
         WC_HIP(hipMemcpyAsync(S.data.get() + off[i0], host.data(), sizeof(double) * host.size(), hipMemcpyHostToDevice,

@@ -48,6 +48,7 @@ __device__ __forceinline__ void gemm_tile(int tri, int& bx, int& by) {
 // accumulator through vector registers at once (the compiler schedules the
 // reads together), which halves the occupancy of the 128 x 128 form, so that
 // form is only instantiated with EPI = 0.
+// NS: sets of staging registers, that is K steps that the loads are issued ahead.
 // tri: 0 every tile; 1 only the lower triangle (row >= col) is written
 // (symmetric rank-k updates); 2 op(A) and op(B) are triangular with
 // op(A)_ik = 0 for k < i and op(B)_kj = 0 for k < j (C = Z^T Z with Z lower
@@ -59,7 +60,7 @@ __device__ __forceinline__ void gemm_tile(int tri, int& bx, int& by) {
 // (76 against 48 for 31 x 31 tiles); mode 3 gives XCD j = id % 8 the
 // contiguous run of tiles starting at j P / 8 (row-major over the triangle),
 // which also keeps tiles that share an A panel on one XCD's L2.
-template <bool TA, bool TB, int BM, int BN, int EPI>
+template <bool TA, bool TB, int BM, int BN, int EPI, int NS>
 __global__ __launch_bounds__(256) void dgemm_kernel(int M, int N, int K, double alpha, const double* __restrict__ A,
                                                     long lda, const double* __restrict__ B, long ldb, double beta,
                                                     double* __restrict__ C, long ldc, int tri, long sA,
@@ -105,8 +106,6 @@ __global__ __launch_bounds__(256) void dgemm_kernel(int M, int N, int K, double 
         if (!TB) { k = idx % GBK; j = idx / GBK; }
         else { j = idx % BN; k = idx / BN; }
     };
-    // NS sets of staging registers: two K steps ahead in the 64 x 64 form
-    constexpr int NS = BM == 64 ? 2 : 1;
     double ras[NS][QA], rbs[NS][QB];
     // Interior tiles with whole K steps load without bounds checks.  Element
     // q of a thread sits a fixed multiple of q leading dimensions past its
@@ -193,7 +192,8 @@ __global__ __launch_bounds__(256) void dgemm_kernel(int M, int N, int K, double 
         if constexpr (NS == 2) {
             // a small product has a workgroup per CU or less, and nothing else
             // to hide a step's loads behind: they are issued two steps ahead
-            // (one step ahead: n = 1000 82 us, now 77; n = 1999 419, now 390)
+            // (one step ahead: n = 1000 82 us, now 77; n = 1999 419, now 390;
+            // two_steps_ahead has the exceptions)
             if (GBK < K) get(0, GBK);
             if (2 * GBK < K) get(1, 2 * GBK);
             __syncthreads();
@@ -452,22 +452,35 @@ static bool dma_ok(bool ta, bool tb, int m, int n, int k, const double* A, long 
            ((!ta && tb) || k % 2 == 0) && std::max(lda, ldb) <= (1L << 21);
 }
 
+// 64 x 64 tiles
+template <bool TA, bool TB, int NS>
+static void dgemm_small_launch(hipStream_t st, dim3 grid, int m, int n, int k, double alpha, const double* A, long lda,
+                               const double* B, long ldb, double beta, double* C, long ldc, int lo, long sA, long sB,
+                               long sC, int klast) {
+    if (beta == 0.0)
+        hipLaunchKernelGGL((dgemm_kernel<TA, TB, GBM, GBN, 1, NS>), grid, dim3(256), dgemm_lds(GBM, GBN), st, m, n, k,
+                           alpha, A, lda, B, ldb, beta, C, ldc, lo, sA, sB, sC, klast);
+    else
+        hipLaunchKernelGGL((dgemm_kernel<TA, TB, GBM, GBN, 2, NS>), grid, dim3(256), dgemm_lds(GBM, GBN), st, m, n, k,
+                           alpha, A, lda, B, ldb, beta, C, ldc, lo, sA, sB, sC, klast);
+}
+
 template <bool TA, bool TB>
 static void dgemm_launch(hipStream_t st, dim3 grid, bool big, int m, int n, int k, double alpha, const double* A,
                          long lda, const double* B, long ldb, double beta, double* C, long ldc, int lo, long sA,
                          long sB, long sC, int klast) {
+    const long wgs = (long)grid.x * grid.y * grid.z / (lo ? 2 : 1);  // a triangle's other tiles leave at once
+    const bool edges = m % GBM != 0 || n % GBN != 0 || k % GBK != 0;
     if (big && dma_ok(TA, TB, m, n, k, A, lda, B, ldb, sA, sB))  // big: only with alpha == 1 and beta == 0
         hipLaunchKernelGGL((dgemm_dma_kernel<TA, TB>), grid, dim3(256), DMA_LDS, st, m, n, k, A, lda, B, ldb, C, ldc,
                            lo, sA, sB, sC);
     else if (big)
-        hipLaunchKernelGGL((dgemm_kernel<TA, TB, GBIG, GBIG, 0>), grid, dim3(256), dgemm_lds(GBIG, GBIG), st, m, n, k,
+        hipLaunchKernelGGL((dgemm_kernel<TA, TB, GBIG, GBIG, 0, 1>), grid, dim3(256), dgemm_lds(GBIG, GBIG), st, m, n, k,
                            1.0, A, lda, B, ldb, 0.0, C, ldc, lo, sA, sB, sC, klast);
-    else if (beta == 0.0)
-        hipLaunchKernelGGL((dgemm_kernel<TA, TB, GBM, GBN, 1>), grid, dim3(256), dgemm_lds(GBM, GBN), st, m, n, k,
-                           alpha, A, lda, B, ldb, beta, C, ldc, lo, sA, sB, sC, klast);
-    else
-        hipLaunchKernelGGL((dgemm_kernel<TA, TB, GBM, GBN, 2>), grid, dim3(256), dgemm_lds(GBM, GBN), st, m, n, k,
-                           alpha, A, lda, B, ldb, beta, C, ldc, lo, sA, sB, sC, klast);
+    else if (two_steps_ahead(TA, TB, edges, wgs))
+        dgemm_small_launch<TA, TB, 2>(st, grid, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, lo, sA, sB, sC, klast);
+    else if constexpr (!TA && TB)
+        dgemm_small_launch<TA, TB, 1>(st, grid, m, n, k, alpha, A, lda, B, ldb, beta, C, ldc, lo, sA, sB, sC, klast);
 }
 
 int dgemm_partials(hipStream_t st, int n, const double* A, long lda, const double* B, long ldb, double* ws,

@@ -44,6 +44,19 @@ inline SplitPlan dgemm_split_plan(int m, int n, int k, long ws_len, int gbm, int
     return p;
 }
 
+// Whether the 64 x 64 form issues its loads two K steps ahead of their use instead
+// of one.  The second set of staging registers costs A B^T its fourth workgroup
+// per CU (152 registers instead of 128), which counts where the launch has edge
+// tiles, whose checked loads end it, and a fourth per CU to run beside them.
+// C -= A B^T in us, two steps ahead and one: n = 1700, 729 workgroups, 227 and 237; n =
+// 1800 330 and 310; n = 2000, k = 100 37.9 and 32.6; n = 3000, 2209 workgroups, 1143 and
+// 1124; n = 4000, 3969 workgroups, 2464 and 2530; without edge tiles n = 2048 322 and
+// 328.  The other products are faster two steps ahead, or the same, at every size
+// (A^T B: n = 1800 306 and 308, n = 3000 1057 and 1121).
+constexpr bool two_steps_ahead(bool ta, bool tb, bool edges, long workgroups) {
+    return ta || !tb || !edges || workgroups <= 3 * 256 || workgroups > 12 * 256;
+}
+
 // Thin product (n <= 16 columns) with B staged in LDS: enough slices that a
 // slice's kc x n block of B fits in thin_lds doubles and, with a workspace,
 // about 2048 workgroups of 64 rows are in flight; at most max_splits.

@@ -100,13 +100,17 @@ constexpr bool entry_small(int n, int r) { return n <= (r <= 4 ? 1024 : 640) && 
 
 // The Lanczos workgroup's split of w = T q: every row in nch chunks of clen
 // columns (the last one shorter), thread t < n nch on row t % n and chunk t / n;
-// one chunk where a row leaves no thread for a second.  Only chunks that start
-// inside the row count: 1024 / n of them would start past it for small n.
+// one chunk where a row leaves no thread for a second.  Chunks have LZ_CHUNK
+// columns at least: shorter ones cost more in the sum over them than they save.  A
+// call in us, as many chunks as there are threads for, 8 columns at least and 16: n =
+// 22 243, 194, 196; n = 32 414, 287, 288 (364 with one thread per row in the
+// reorthogonalisation); n = 64 516, 444, 417; n = 100 626, 616, 571; n = 200 867, 862, 854.
 // Its dynamic LDS in doubles: q (n, then LZ_TREG zeros, which a thread's
 // register columns past the row's end are multiplied with: cl0 + u <= n - 1 +
 // LZ_TREG - 1), w (n) at `w`, partial sums (n nch) at `pp`, the basis at `Q`.
 constexpr int LZ_THREADS = 1024;
-constexpr int LZ_TREG = 24;  // columns of its chunk of T that a thread keeps in registers
+constexpr int LZ_TREG = 24;   // columns of its chunk of T that a thread keeps in registers
+constexpr int LZ_CHUNK = 16;  // columns of a chunk at least
 
 struct LanczosPlan {
     int nch, clen;
@@ -115,7 +119,7 @@ struct LanczosPlan {
 
 constexpr LanczosPlan lanczos_plan(int n) {
     LanczosPlan p{};
-    const int most = n > LZ_THREADS / 2 ? 1 : LZ_THREADS / n;
+    const int most = n > LZ_THREADS / 2 ? 1 : std::min(LZ_THREADS / n, (n + LZ_CHUNK - 1) / LZ_CHUNK);
     p.clen = (n + most - 1) / most;
     p.nch = (n + p.clen - 1) / p.clen;
     p.w = n + LZ_TREG;

@@ -28,7 +28,9 @@ int main() {
     for (int n = 1; n <= 640; ++n) {
         const LanczosPlan p = lanczos_plan(n);
         bool ok = p.nch >= 1 && p.w >= n + LZ_TREG && p.pp >= p.w + n && p.Q >= p.pp + (p.nch > 1 ? n * p.nch : 0);
-        ok = ok && n * p.nch <= std::max(n, LZ_THREADS) && (n > LZ_THREADS / 2) == (p.nch == 1 && n > 1);
+        ok = ok && n * p.nch <= std::max(n, LZ_THREADS) && (p.nch == 1) == (n > LZ_THREADS / 2 || n <= LZ_CHUNK);
+        // no chunk but the last shorter than half of LZ_CHUNK
+        ok = ok && (p.nch == 1 || 2 * p.clen > LZ_CHUNK);
         std::vector<int> seen(n, 0);  // columns of row 0
         if (p.nch == 1) std::fill(seen.begin(), seen.end(), 1);
         for (int tid = 0; tid < LZ_THREADS && p.nch > 1; ++tid) {
@@ -61,4 +63,4 @@ def test_lanczos_reads_stay_inside_the_vector_and_its_zeros(tmp_path):
     subprocess.run([cxx, "-std=c++17", "-O1", "-I", CSRC, str(src), "-o", str(exe)], check=True)
     r = subprocess.run([str(exe)], capture_output=True, text=True)
     assert r.returncode == 0, r.stdout[-2000:]
-    assert int(r.stdout.split()[-3]) > 1_000_000
+    assert int(r.stdout.split()[-3]) > 500_000

@@ -37,6 +37,7 @@
 
 #include "batched.hpp"
 #include "host_pool.hpp"
+#include "launch_plan.hpp"
 #include "sdp_kernels.hpp"
 #include "wave.hpp"
 
@@ -1843,12 +1844,10 @@ void stage(const sdp_problem* probs, int count, const sdp_options& o, hipStream_
         I.n = n;
         I.m = m;
         I.rmax = std::max(1, std::min(o.rank_max, n - 1));
-        // without a tuning: short packed rows take 16 lanes each (a row of n = 24
-        // is 150 pairs), and n < 48 leaves most of the eight waves without a
-        // 32 x 32 tile
-        I.rows_per_wave = tune ? tune[i].rows_per_wave : (n < 48 ? 4 : 2);
+        const BatchForm form = batch_form(n);  // without a tuning
+        I.rows_per_wave = tune ? tune[i].rows_per_wave : form.rows_per_wave;
         I.aq_group = tune ? tune[i].aq_group : 8;
-        I.gemm_tile = tune ? (tune[i].gemm_tile ? tune[i].gemm_tile : 32) : (n < 48 ? 16 : 32);
+        I.gemm_tile = tune ? (tune[i].gemm_tile ? tune[i].gemm_tile : 32) : form.gemm_tile;
         require(I.rows_per_wave >= 1 && I.rows_per_wave <= 4 && I.aq_group >= 1 && I.aq_group <= 16 &&
                     (I.gemm_tile == 16 || I.gemm_tile == 32),
                 "batch tune out of range (rows_per_wave 1..4, aq_group 1..16, gemm_tile 0, 16 or 32)");
@@ -2012,9 +2011,8 @@ void autotune_batched(const sdp_problem* probs, int count, const sdp_options* op
     else sdp_default_options(&o);
     o.max_ipm_iter = 2;  // time the first iterations only
     // pass settings x the wave tile of the workgroup's MFMA products; 16 x 16
-    // wave tiles are tried only where 32 x 32 ones leave waves idle (n < 48:
-    // at most four tiles for the four waves), since elsewhere they only add
-    // operand reads
+    // wave tiles are the faster ones up to n = 32 (batch_form), so they are tried
+    // in the first bucket only
     const BatchTune cands[] = {{1, 4, 32}, {2, 8, 32}, {4, 8, 32}, {4, 16, 32},
                                {1, 4, 16}, {2, 8, 16}, {4, 8, 16}, {4, 16, 16}};
     const int ncand_all = sizeof(cands) / sizeof(cands[0]);

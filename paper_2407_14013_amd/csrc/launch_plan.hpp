@@ -1,8 +1,11 @@
 // Launch arithmetic of the split-K FP64 products (blas.hip), of the operator's
-// forms for dense rows and entry sampling (dense_op.hip, entry_op.hip) and of the Lanczos workgroup (lanczos.hip), free of HIP so that host code -- including
-// host-compiled tests that enumerate shapes -- can evaluate it.  A split-K plan splits K into `splits` slices of kc values; the
-// last slice takes the remainder klast = K - (splits - 1) kc, 1 <= klast <= kc,
-// so slice s reads operand columns (or rows) s kc .. s kc + (its K) - 1 only.
+// forms for dense rows and entry sampling (dense_op.hip, entry_op.hip), of the
+// batched solver (batched.hip) and of the Lanczos workgroup (lanczos.hip), free
+// of HIP so that host code -- including host-compiled tests that enumerate
+// shapes -- can evaluate it.  A split-K plan splits K into `splits` slices of kc
+// values; the last slice takes the remainder klast = K - (splits - 1) kc, 1 <=
+// klast <= kc, so slice s reads operand columns (or rows) s kc .. s kc + (its K)
+// - 1 only.
 #pragma once
 
 #include <algorithm>
@@ -97,6 +100,17 @@ constexpr bool dense_explicit(long m, long d) { return m * d <= 20'000'000; }
 // 142 at n = 300, 173 and 174 at n = 640, 199 and 187 at n = 768, 269 and 230 at n = 1024.
 constexpr int EN_R = 16;  // most columns of Q in one launch
 constexpr bool entry_small(int n, int r) { return n <= (r <= 4 ? 1024 : 640) && r <= EN_R && n * r <= 8192; }
+
+// The batched solver's pass settings for an instance without a tuning: packed rows
+// that a wave streams at once and the edge of its MFMA tiles.  Up to n = 32 the
+// 32 x 32 tiles are at most one for eight waves, and a packed row is short (528
+// entries at n = 32).  Four iterations of 32 instances in ms, 4 rows with 16 x 16
+// tiles and 2 rows with 32 x 32: n = 16 26.3 and 27.1, n = 32 38.1 and 39.5, n = 33 46.9
+// and 45.8, n = 40 53.6 and 47.8, n = 47 81.2 and 75.7, n = 72 208 and 189.
+struct BatchForm {
+    int rows_per_wave, gemm_tile;
+};
+constexpr BatchForm batch_form(int n) { return n <= 32 ? BatchForm{4, 16} : BatchForm{2, 32}; }
 
 // The Lanczos workgroup's split of w = T q: every row in nch chunks of clen
 // columns (the last one shorter), thread t < n nch on row t % n and chunk t / n;

@@ -18,27 +18,12 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef unsigned short v8us __attribute__((ext_vector_type(8)));
 typedef double ld2 __attribute__((ext_vector_type(2)));
 typedef float lf4 __attribute__((ext_vector_type(4)));
-typedef float lf2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ unsigned short bf16_rne(float f) {
     unsigned u = __float_as_uint(f);
     if ((u & 0x7fffffffu) > 0x7f800000u) return static_cast<unsigned short>((u >> 16) | 0x40u);  // quiet NaN
     u += 0x7fffu + ((u >> 16) & 1u);
     return static_cast<unsigned short>(u >> 16);
-}
-
-template <int BS>
-__device__ __forceinline__ double lp_block_sum(double v, double* sh) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane == 0) sh[wv] = v;
-    __syncthreads();
-    double s = 0.0;
-#pragma unroll
-    for (int i = 0; i < BS / 64; ++i) s += sh[i];
-    return s;
 }
 
 // ---- GEMM epilogue -----------------------------------------------------------------
@@ -371,7 +356,7 @@ __global__ __launch_bounds__(512, 2) void bgemm_sym256_kernel(int M, int N, cons
     xcd_tile(tiles_m, tiles_n, tm, tn);
     const int row0 = tm * BT, col0 = tn * BT;
     const int full = K / 32;  // steps whose 32 k-values are all in range
-    // load instruction h of wave wv covers c = wv + 4 h: A rows (c < 16) or B columns
+    // load instruction h of wave wv covers c = wv + 8 h: A rows (c < 16) or B columns
     // 16 (c % 16) .. + 15; lane l fills row l / 4, stage position l % 4
     const unsigned short* src[4];
     {

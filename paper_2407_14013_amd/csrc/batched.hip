@@ -24,8 +24,8 @@
 // (held in scalar registers over the whole method they spilled at every use,
 // and untyped they made every access a flat one).  256 instances with n in
 // [16, 24]: 1 120 ms with 256 threads and one load or one product per phase,
-// 258 ms in this form; one instance of n = 24, m = 216: 242 to 54 us per
-// Krylov iteration; n = 128, m = 1152: 16.0 to 3.2 s per solve.
+// 210 to 250 ms in this form; one instance of n = 24, m = 216: 242 to 54 us per
+// Krylov iteration, all else included; n = 128, m = 1152: 16.0 to 2.8 s per solve.
 #include <algorithm>
 #include <atomic>
 #include <chrono>

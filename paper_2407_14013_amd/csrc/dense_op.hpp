@@ -6,7 +6,10 @@
 
 namespace wc {
 
-// Largest n for which dense_mid runs (its three matrices fill the LDS of a CU).
+// Largest n for which dense_mid runs: past it one workgroup takes longer than the
+// launches it saves.  newton_apply in us, with it and with the products split over
+// the chip: n = 16 13 and 24, n = 40 23 and 32, n = 64 32 and 37 (m = 1664 37 and 41), n =
+// 65 39 and 38 (m = 1716 47 and 41), n = 80 46 and 43.
 constexpr int DENSE_MID_N = 64;
 
 // mw = packed weights of E Y E (zero past N2, ldp entries), with Y = A^T(u) given

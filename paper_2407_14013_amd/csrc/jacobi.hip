@@ -264,8 +264,9 @@ __device__ __forceinline__ void cross_steps(F f) {
 // matrices (n = 48 .. 300), a decomposition takes 0 to 2 more sweeps of 8 to
 // 17.  Bound by the ~166 instructions one wave issues per step (the angle's and
 // the 64 of H's update), everything in registers: with R's 32 in the same wave a
-// pass took 6.1 us and a round at n = 200 19.5; with R in a second wave 18.5.  Every thread of
-// the workgroup calls this (one barrier per step); cs is a 16 x 32 work array.
+// pass took 6.1 us and a round at n = 200 that rotates every pair 19.5; with R in a
+// second wave 17.9.  Every thread of the workgroup calls this (one barrier per
+// step); cs is a 16 x 32 work array.
 __device__ __forceinline__ void cross_jacobi(const double (*H)[JW + 1], double (*cs)[JW + 1], double (*R)[JW + 1]) {
     const int lane = threadIdx.x & 63, l = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // a scalar: the waves part ways
@@ -592,9 +593,9 @@ __global__ __launch_bounds__(256) void jacobi_rotate_kernel(int n, int nblk, int
 // A round has only nblk / 2 workgroups (7 at n = 200), so it is bound by the
 // latency of one workgroup's chain: load, Gram matrix, inner rotations,
 // rotation.  Eight waves: the first four take A, the others V, whose loads
-// land while the Gram matrix forms.  At n = 200 a round takes 15.7 us; it was
-// 27.8 us with all 496 pairs rotated in every round and four waves walking A,
-// then V.
+// land while the Gram matrix forms.  Over the solves at n = 200 a round takes
+// 15.3 us on average (17.9 where every pair is rotated); it was 27.8 us with all 496
+// pairs rotated in every round and four waves walking A, then V.
 // ---------------------------------------------------------------------------
 __host__ __device__ inline int jl_ld(int n) { return ((n + 15) / 16) * 16 + 1; }  // odd pitch: fewer bank conflicts
 

@@ -1,6 +1,6 @@
 // Smallest eigenvalue of a symmetric n x n matrix by the Lanczos process with
 // full reorthogonalisation, run by one 1024-thread workgroup (n <= 4096; the
-// basis is kept in LDS for n up to about 240).
+// basis is kept in LDS for n up to about 280).
 //
 // Used for the interior-point step length: the largest alpha with
 // L L^T + alpha D PSD is 1 / max(0, -lambda_min(L^{-1} D L^{-T})).  The
